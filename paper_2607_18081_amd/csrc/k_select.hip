@@ -4,7 +4,7 @@
 //  - act_rows: the activation a[t][j] = SiLU(gate_j . x_t) * (up_j . x_t) of every loaded slot
 //    for any storage type (one wave per (token, slot)); bf16 data use the MFMA tiles of
 //    k_tiled.hip instead;
-//  - col_abs_sum / add_rows: Eq. 1 sums |a| over tokens (float32 over at most 256 tokens) and
+//  - col_abs_sum / add_rows: Eq. 1 sums |a| over tokens (one float32 per at most 256 tokens) and
 //    the partial rows of the token tiles in float64, in ascending order, into float64 scores;
 //  - count_bits: how many tokens select each slot, from the tokens' top-alpha bitmaps (up to
 //    32768 slots): one work-group per 32-slot word, wave ballots and a fixed-order sum, so the

@@ -237,6 +237,48 @@ def test_union_tiled_k_step_counts(d):
         assert max_rel_l2(exact, want) <= ALARM_PER_TOKEN, nU
 
 
+@pytest.mark.parametrize("B,L,d,step", [
+    # GEMM1 tiles (tokens x weight rows) by what fills the CUs: 128 x 160, 256 x 160, 256 x 256
+    (130, 1290, 8, 1), (512, 5300, 72, 1), (1100, 5300, 136, 1),
+    # K steps around one, two and three turns of the LDS stages, whole and ragged
+    (512, 5300, 192, 1), (512, 5300, 264, 1), (1100, 5300, 384, 1), (1100, 5300, 456, 1),
+    (1100, 5300, 832, 1), (200, 1290, 320, 1), (200, 1290, 520, 1),
+    # slots so far apart that a tile's mask words do not fit its LDS window
+    (1100, 5300, 136, 7), (512, 5300, 72, 9), (130, 9000, 136, 40),
+    # GEMM2's 256 x 256 tile and split K, a ragged last column tile
+    (2048, 5500, 4088, 1)])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_union_tiled_tiles(B, L, d, step, dt):
+    """Every tile of the tiled GEMMs at ragged token, slot, column and K edges, against the
+    definition in float64 on the GPU. Rounding h to one 16-bit value leaves 2^-9 (bf16) or 2^-12
+    (half) of each product at most, so the sums agree to that relative to their 2-norm; the hi +
+    lo pair to 1e-4 as elsewhere."""
+    say(f"tiled tiles B={B} L={L} d={d} every {step} {dt}")
+    g = torch.Generator(device="cuda").manual_seed(B + L + d + step)
+    r = lambda s, *sh: torch.empty(sh, device="cuda").normal_(0, s, generator=g).to(dt)
+    gu, dn, x = r(d ** -0.5, L, 2, d), r(d ** -0.5, L, d), r(1.0, B, d)
+    pool = torch.arange(L % step, L, step, device="cuda")
+    keep = torch.rand((B, len(pool)), device="cuda", generator=g) < 0.3
+    keep[3] = False                                       # an empty set
+    keep[5] = True                                        # the union is the whole pool
+    off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+    off[1:] = keep.sum(1).cumsum(0)
+    idx = pool.expand(B, -1)[keep].to(torch.int32)
+    mask = torch.zeros((B, L), dtype=torch.bool, device="cuda")
+    mask[:, pool] = keep
+    xx = x.double()
+    h = torch.nn.functional.silu(xx @ gu[:, 0].double().t()) * (xx @ gu[:, 1].double().t())
+    want = torch.where(mask, h, 0.0) @ dn.double()
+    for flags, tol in ((0, 2.0 ** (-9 if dt == torch.bfloat16 else -12)),
+                       (si.FLAG_EXACT_H, 1e-4)):
+        got = si.selective_ffn(x, off, idx, gu, dn, flags=flags)
+        assert not got[3].any()
+        err = ((got - want).norm() / want.norm()).item()
+        say(f"  flags {flags}: {err:.2e}")
+        assert err <= tol
+        assert torch.equal(got, si.selective_ffn(x, off, idx, gu, dn, flags=flags))
+
+
 @pytest.mark.parametrize("seed", range(24))
 def test_random_shapes(seed):
     """Seeded random problems across the path boundaries: B from 1 to 300 (per-token below 5
