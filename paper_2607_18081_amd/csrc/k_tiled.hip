@@ -38,22 +38,15 @@
 #include <hip/hip_ext.h>
 
 #include <atomic>
-#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
-#include "mfma.h"
-#include "pipe.h"
+#include "gemm_pipe.h"
 #include "selectinfer.h"
 
 namespace si {
 
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
-
-constexpr int kBK = 64;          // K step (elements)
 
 // part[c][w] = OR of bits[b][w] over the 64 tokens b of block c. Work-group (wx, c): 64 words
 // x 64 tokens; each wave ORs 16 tokens of the 64 words, then the 4 waves meet in LDS.
@@ -135,610 +128,6 @@ __global__ __launch_bounds__(1024) void union_scan(const uint32_t* __restrict__ 
         }
     }
     if (t == 0) *ucount = all;
-}
-
-// ---- GEMM1 ---------------------------------------------------------------------------------
-// MODE selects what the epilogue produces (the product itself is the same):
-//   kUnion:  h masked by the token bitmaps, over the union list, as 16-bit hi (and lo) planes;
-//   kAct:    the activation of every slot (the union list is the identity, no mask), float32
-//            out[tok * Up + slot];
-//   kScore:  Eq. 1 for this work-group's tokens: sum over its BM tokens of |a| per slot, added
-//            in a fixed order, float32 out[tm * Up + slot] (one partial row per token tile; the
-//            host-side reducer adds the rows in order).
-enum { kUnion = 0, kAct = 1, kScore = 2 };
-
-// Token bitmap words a work-group keeps in LDS for the mask (per token; pitch odd so that 16
-// tokens' words lie in different banks)
-constexpr int kWin = 16, kWinP = kWin + 1;
-
-// BM tokens x BN weight rows (BN / 2 union slots); WT x WW waves of FT x FW 16x16 MFMA tiles,
-// the weight rows as the M operand, so a lane ends up with 4 consecutive weight rows of one
-// token. Those are 2 gate and 2 up rows of the same two slots, so SiLU * up needs no data
-// exchange. NX LDS stages of x and NWT of the weight rows, which come from HBM and are given
-// the longer flight where the LDS cannot hold a third stage of both (256 x 256).
-template <typename ET, int MODE, int BM, int BN, int WT, int WW, int NX, int NWT>
-__global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
-    const uint16_t* __restrict__ x, int64_t B, int64_t d, const uint16_t* __restrict__ gu, int64_t L,
-    const int32_t* __restrict__ ulist, const int* __restrict__ ucount,
-    const uint32_t* __restrict__ bits, int64_t W, uint16_t* __restrict__ Hhi,
-    uint16_t* __restrict__ Hlo, int64_t Up, int ntm, float* __restrict__ out) {
-    constexpr int NW = WT * WW, kThr = 64 * NW;
-    constexpr int FT = BM / (16 * WT), FW = BN / (16 * WW);
-    constexpr int kS = BN / 2;
-    // 1 KB pieces (8 rows) of a stage, and how many of them a wave loads (the last of a
-    // wave's weight pieces may be left to the lower waves: kPart of them)
-    constexpr int RX = BM / 8, RW = BN / 8, LX = RX / NW, LW = RW / NW, kPart = RW % NW;
-    constexpr bool kSplit = NWT > NX;
-    constexpr int kPer = kSplit ? NX * NWT : NX;  // steps after which the stages come round
-    static_assert(RX % NW == 0 && NX >= 2 && NX <= 4, "tile");
-    static_assert(NWT == NX || (NX == 2 && NWT == 3 && kPart == 0), "stages");
-    typedef typename Mfma<ET>::vec8 vec8;
-    // one array per stage: the compiler then sees that a stage's reads do not touch the stages
-    // being loaded, and waits for nothing between them
-    __shared__ __align__(1024) char x0[RX * 1024];
-    __shared__ __align__(1024) char x1[RX * 1024];
-    __shared__ __align__(1024) char x2[NX > 2 ? RX * 1024 : 16];
-    __shared__ __align__(1024) char x3[NX > 3 ? RX * 1024 : 16];
-    __shared__ __align__(1024) char w0[RW * 1024];
-    __shared__ __align__(1024) char w1[RW * 1024];
-    __shared__ __align__(1024) char w2[NWT > 2 ? RW * 1024 : 16];
-    __shared__ __align__(1024) char w3[NWT > 3 ? RW * 1024 : 16];
-
-    const int nU = MODE == kUnion ? *ucount : (int)L;
-    int tm, st;
-    if (!xcd_tile((int)blockIdx.x, ntm, (nU + kS - 1) / kS, tm, st)) return;  // uniform
-    const int64_t m0 = (int64_t)tm * BM, u0 = (int64_t)st * kS;
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int nn = lane & 15;
-    const int g = lane >> 4;
-    const int wt = w % WT, ww = w / WT;
-
-    // slot of union position u0 + p, -1 past the union
-    const __amdgpu_buffer_rsrc_t rul = make_rsrc(ulist, MODE == kUnion ? (int64_t)nU * 4 : 0);
-    auto union_slot = [&](int p) -> int32_t {
-        const int u = (int)u0 + p;
-        int32_t sl = u;
-        if constexpr (MODE == kUnion)
-            sl = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rul, u * 4, 0, 0);
-        return (u < nU && (unsigned)sl < (unsigned)L) ? sl : -1;
-    };
-    // weight row 16 f + 4 q + e of the tile (e < 4): plane e / 2 (gate, up) of slot
-    // slot_of(f, q, e % 2). A wave's tiles f come in pairs, over which a lane's slots are four
-    // consecutive ones (an odd last tile: two), for wide stores of h.
-    auto slot_of = [&](int f, int q, int e) {
-        const int i = f % FW, base = (f / FW) * 8 * FW;
-        return i < (FW & ~1) ? base + 16 * (i / 2) + 4 * q + 2 * (i & 1) + e
-                             : base + 8 * i + 2 * q + e;
-    };
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x, B * d * 2);
-    const __amdgpu_buffer_rsrc_t rg = make_rsrc(gu, L * 2 * d * 2);
-    // Piece p: rows 8 p + lane / 8, 128 bytes (a K step) each. The 16-byte chunk c of row r is
-    // kept at position c ^ (r % 8), so that the fragment reads of 16 rows at one chunk meet no
-    // bank conflicts; the loads place it so by what each lane reads.
-    const int cb = ((lane & 7) ^ (lane >> 3)) * 16;
-    int xoff[LX], woff[LW + 1];
-#pragma unroll
-    for (int j = 0; j < LX; ++j) {
-        const int64_t tok = m0 + 8 * (j * NW + w) + (lane >> 3);
-        xoff[j] = tok < B ? (int)(tok * d * 2) + cb : kOOB;
-    }
-#pragma unroll
-    for (int j = 0; j < LW + (kPart ? 1 : 0); ++j) {
-        const int r = 8 * (j * NW + w) + (lane >> 3);  // (past the tile: not loaded)
-        const int32_t sl = union_slot(slot_of(r / 16, (r % 16) / 4, r & 1));
-        woff[j] = sl >= 0 ? (int)(((int64_t)sl * 2 + ((r >> 1) & 1)) * d * 2) + cb : kOOB;
-    }
-    // the mask's window: kWin bitmap words from the first slot's on, unless the tile's slots
-    // span more
-    int win0 = 0;
-    bool in_win = false;
-    if constexpr (MODE == kUnion) {
-        const int last = (int)(nU - u0 < kS ? nU - u0 : kS) - 1;
-        win0 = __builtin_amdgcn_readfirstlane(ulist[u0] >> 5);
-        in_win = __builtin_amdgcn_readfirstlane(ulist[u0 + last] >> 5) - win0 < kWin;
-    }
-
-    const int nk = (int)((d + kBK - 1) / kBK);
-    // loads of step k into stage s: what lies past d reads as zeros (d % 8 == 0: a chunk is all
-    // in or all out)
-    auto load_x = [&](int k, char* s) {
-        const bool ok = k * 128 + cb < (int)(d * 2);
-#pragma unroll
-        for (int j = 0; j < LX; ++j)
-            load_lds16(rx, s + (j * NW + w) * 1024, ok ? xoff[j] : kOOB, k * 128);
-    };
-    auto load_w = [&](int k, char* s) {
-        const bool ok = k * 128 + cb < (int)(d * 2);
-#pragma unroll
-        for (int j = 0; j < LW; ++j)
-            load_lds16(rg, s + (j * NW + w) * 1024, ok ? woff[j] : kOOB, k * 128);
-    };
-    // the pieces that only waves below kPart have: loaded before the others of the same step,
-    // so that the counted waits hold for every wave
-    auto load_part = [&](int k, char* s) {
-        if constexpr (kPart != 0) {
-            const bool ok = k * 128 + cb < (int)(d * 2);
-            if (w < kPart)
-                load_lds16(rg, s + (LW * NW + w) * 1024, ok ? woff[LW] : kOOB, k * 128);
-        }
-    };
-
-    f32x4_t acc[FW][FT];
-#pragma unroll
-    for (int i = 0; i < FW; ++i)
-#pragma unroll
-        for (int j = 0; j < FT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // fragments of the two halves (K = 32) of a step
-    vec8 ft[2][FT], fw[2][FW];
-    const int to = (wt * 16 * FT + nn) * 128, wo = (ww * 16 * FW + nn) * 128;
-    const int c0 = (g ^ (nn & 7)) * 16, c1 = ((4 + g) ^ (nn & 7)) * 16;
-    auto frags = [&](const char* sx, const char* sw, int h) {
-        const int c = h ? c1 : c0;
-#pragma unroll
-        for (int i = 0; i < FW; ++i) fw[h][i] = Mfma<ET>::vec(ld16(sw + wo + i * 2048 + c));
-#pragma unroll
-        for (int j = 0; j < FT; ++j) ft[h][j] = Mfma<ET>::vec(ld16(sx + to + j * 2048 + c));
-    };
-    auto mults = [&](int h) {
-#pragma unroll
-        for (int j = 0; j < FT; ++j)
-#pragma unroll
-            for (int i = 0; i < FW; ++i) acc[i][j] = Mfma<ET>::mma(fw[h][i], ft[h][j], acc[i][j]);
-    };
-    char* const xs[4] = {x0, x1, x2, x3};
-    char* const ws[4] = {w0, w1, w2, w3};
-    // One K step k = q mod kPer. The first half's fragments are in registers. The second half's
-    // are read under the first half's MFMAs; then every wave has read all of step k's stages
-    // and, past the barrier, they take the loads of step k + NX (k + NWT), while the next
-    // step's first fragments are read under the second half's MFMAs. One barrier a step, and
-    // every wave holds the fragments of half a step when it meets it. With kSplit the weight
-    // loads go out in the next step's first half instead: behind the x loads, so that a wait
-    // for those leaves the later weight loads in flight.
-    constexpr int NM = FT * FW, NR = FT + FW;
-    constexpr int LA = kSplit ? LW : 0, LB = LX + (kSplit ? 0 : LW);  // loads in each half
-    auto step = [&](int k, int q) {
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kSplit) load_w(k - 1 + NWT, ws[(q + NWT - 1) % NWT]);
-        frags(xs[q % NX], ws[q % NWT], 1);
-        mults(0);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {  // one LDS read (and load), then its share of the MFMAs
-            if (i < LA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, NM / NR, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vm_lds<kSplit ? LW : (NX - 2) * (LX + LW)>();  // the next step's loads have landed
-        wg_barrier();
-        load_part(k + NWT, ws[q % NWT]);
-        __builtin_amdgcn_sched_barrier(0);
-        load_x(k + NX, xs[q % NX]);
-        if constexpr (!kSplit) load_w(k + NWT, ws[q % NWT]);
-        frags(xs[(q + 1) % NX], ws[(q + 1) % NWT], 0);
-        mults(1);
-#pragma unroll
-        for (int i = 0; i < (NR > LB ? NR : LB); ++i) {
-            if (i < LB) {
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-            if (i < NR) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-        }
-        asm volatile("" ::: "memory");
-    };
-    // (with kSplit a step's first half issues the weights of step k + NWT - 1: those of step
-    // NWT - 1 are left to step 0)
-#pragma unroll
-    for (int q = 0; q < NX; ++q) {
-        load_part(q, ws[q]);
-        load_x(q, xs[q]);
-        load_w(q, ws[q]);
-        __builtin_amdgcn_sched_barrier(0);  // the counted waits rely on the stages' order
-    }
-    wait_vm_lds<(NX - 1) * (LX + LW)>();
-    wg_barrier();
-    frags(x0, w0, 0);
-    int k = 0;
-    for (; k + kPer <= nk; k += kPer) {
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) step(k + q, q);
-    }
-#pragma unroll
-    for (int q = 0; q < kPer - 1; ++q)
-        if (k + q < nk) step(k + q, q);
-
-    // The stages are done with (nothing is in flight to them either): their memory takes the
-    // epilogue's tables.
-    wait_vm_lds<0>();
-    wg_barrier();
-    int32_t* const sslot = reinterpret_cast<int32_t*>(w0);       // the tile's slots
-    uint32_t* const swin = reinterpret_cast<uint32_t*>(x0);      // the mask's window
-    double* const ssum = reinterpret_cast<double*>(x0);          // kScore: sums per wave row
-    static_assert(BM * kWinP * 4 <= RX * 1024 && WT * kS * 8 <= RX * 1024 && kS <= kThr, "tables");
-    if (t < kS) sslot[t] = union_slot(t);
-    if constexpr (MODE == kUnion) {
-        if (in_win) {
-            const __amdgpu_buffer_rsrc_t rbm = make_rsrc(bits, B * W * 4);
-            constexpr int kWinQ = BM * kWin / kThr;
-            uint32_t v[kWinQ];
-#pragma unroll
-            for (int q = 0; q < kWinQ; ++q) {
-                const int e = q * kThr + t, wi = win0 + e % kWin;
-                const int64_t tok = m0 + e / kWin;
-                v[q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                    rbm, (tok < B && wi < W) ? (int)((tok * W + wi) * 4) : kOOB, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < kWinQ; ++q) {
-                const int e = q * kThr + t;
-                swin[(e / kWin) * kWinP + e % kWin] = v[q];
-            }
-        }
-    }
-    __syncthreads();
-
-    // element e of acc[i][j]: plane e / 2 of slot slot_of(ww FW + i, g, e % 2) for token
-    // m0 + 16 (wt FT + j) + nn
-    if constexpr (MODE == kScore) {
-        // |a| summed over this lane's tokens, the 16 lanes nn, then the WT waves, each in a
-        // fixed order, in float64 and rounded once (a few hundred adds a work-group; float32
-        // sums of 256 tokens were 6.1e-8 from the 64-bit scores, of 128 tokens 5.7e-8)
-#pragma unroll
-        for (int i = 0; i < FW; ++i)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                double v = 0.0;
-#pragma unroll
-                for (int j = 0; j < FT; ++j) {
-                    const int64_t tok = m0 + 16 * (wt * FT + j) + nn;
-                    if (tok < B) v += (double)fabsf(silu_f32(acc[i][j][e]) * acc[i][j][2 + e]);
-                }
-                v += __shfl_xor(v, 1, kWave);
-                v += __shfl_xor(v, 2, kWave);
-                v += __shfl_xor(v, 4, kWave);
-                v += __shfl_xor(v, 8, kWave);
-                if (nn == 0) ssum[wt * kS + slot_of(ww * FW + i, g, e)] = v;
-            }
-        __syncthreads();
-        if (t < kS && u0 + t < nU) {
-            double a = ssum[t];
-#pragma unroll
-            for (int q = 1; q < WT; ++q) a += ssum[q * kS + t];
-            out[(int64_t)tm * Up + u0 + t] = (float)a;
-        }
-        return;
-    }
-    const __amdgpu_buffer_rsrc_t rbm = make_rsrc(bits, MODE == kUnion ? B * W * 4 : 0);
-    auto finish = [&](auto win) {
-        constexpr int kLast = FW & 1 ? FW - 1 : FW;
-#pragma unroll
-        for (int i = 0; i < FW; i += 2) {
-            const int np = i == kLast ? 1 : 2;  // tiles of this pair: 2 np consecutive slots
-            const int64_t u = u0 + slot_of(ww * FW + i, g, 0);
-            int32_t sl[4];
-#pragma unroll
-            for (int e = 0; e < 2 * np; ++e) sl[e] = sslot[slot_of(ww * FW + i, g, 0) + e];
-#pragma unroll
-            for (int j = 0; j < FT; ++j) {
-                const int row = 16 * (wt * FT + j) + nn;
-                const int64_t tok = m0 + row;
-                float h[4];
-#pragma unroll
-                for (int e = 0; e < 2 * np; ++e) {
-                    const f32x4_t& c = acc[i + e / 2][j];
-                    h[e] = silu_f32(c[e & 1]) * c[2 + (e & 1)];
-                }
-                if constexpr (MODE == kAct) {
-                    float* o = out + tok * Up + u;  // Up is a multiple of 4
-                    if (tok < B && np == 2 && sl[3] >= 0) {
-                        *reinterpret_cast<f32x4_t*>(o) = f32x4_t{h[0], h[1], h[2], h[3]};
-                    } else if (tok < B) {
-#pragma unroll
-                        for (int e = 0; e < 2 * np; ++e)
-                            if (sl[e] >= 0) o[e] = h[e];
-                    }
-                } else {
-                    uint32_t hb[4], lb[4];
-#pragma unroll
-                    for (int e = 0; e < 2 * np; ++e) {
-                        // a slot past the union, or one that is not in the token's set: h = 0
-                        const int wi = sl[e] >> 5;
-                        uint32_t word;
-                        if constexpr (decltype(win)::value)
-                            word = swin[row * kWinP + ((wi - win0) & (kWin - 1))];
-                        else
-                            word = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                                rbm, (tok < B && sl[e] >= 0) ? (int)((tok * W + wi) * 4) : kOOB, 0,
-                                0);
-                        const bool act = sl[e] >= 0 && ((word >> (sl[e] & 31)) & 1u);
-                        h[e] = act ? h[e] : 0.0f;
-                        hb[e] = Mfma<ET>::rne(h[e]);
-                        lb[e] = Mfma<ET>::rne(h[e] - Mfma<ET>::widen(hb[e]));
-                    }
-                    // up to the end of this tile, so that the 8-wide chunk of GEMM2 that
-                    // straddles the union's end holds zeros past it (Up is a multiple of 64)
-                    if (tok < B && u < Up) {
-                        uint32_t* ph = reinterpret_cast<uint32_t*>(Hhi + tok * Up + u);
-#pragma unroll
-                        for (int e = 0; e < np; ++e) ph[e] = hb[2 * e] | (hb[2 * e + 1] << 16);
-                        if (Hlo) {  // the lo plane exists only for SI_FLAG_EXACT_H
-                            uint32_t* pl = reinterpret_cast<uint32_t*>(Hlo + tok * Up + u);
-#pragma unroll
-                            for (int e = 0; e < np; ++e) pl[e] = lb[2 * e] | (lb[2 * e + 1] << 16);
-                        }
-                    }
-                }
-            }
-        }
-    };
-    if (MODE != kUnion || in_win)
-        finish(std::true_type());
-    else
-        finish(std::false_type());  // the tile's slots span more than kWin bitmap words
-}
-
-// ---- GEMM2 ---------------------------------------------------------------------------------
-// BM tokens x BN columns of Y over one of KS chunks of the union, K = union position in steps
-// of 64; WT x WW waves of FT x FW 16x16 MFMA tiles, the columns as the M operand, so a lane ends
-// up with 4 consecutive columns of one token (16-byte stores). PL planes of H (1: one 16-bit
-// value, 2: hi + lo). Chunk 0 goes to y, chunk p > 0 to row p - 1 of the partials.
-template <typename ET, int PL, int BM, int BN, int WT, int WW, int NH, int ND>
-__global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
-    const uint16_t* __restrict__ Hhi, const uint16_t* __restrict__ Hlo, int64_t Up, int64_t B,
-    const uint16_t* __restrict__ dc, int64_t d, int64_t L, const int32_t* __restrict__ ulist,
-    const int* __restrict__ ucount, float* __restrict__ y, float* __restrict__ part, int KS,
-    int ntm, int ntn) {
-    constexpr int NW = WT * WW;
-    constexpr int FT = BM / (16 * WT), FW = BN / (16 * WW);
-    // 1 KB pieces of a stage and how many of them a wave loads
-    constexpr int RH = PL * BM / 8, RD = BN / 8, LH = RH / NW, LD = RD / NW;
-    constexpr bool kSplit = ND > NH;
-    constexpr int kPer = kSplit ? NH * ND : NH;  // steps after which the stages come round
-    constexpr int kRow = 2 * BN;                 // bytes of a down row segment
-    constexpr int kRpp = 1024 / kRow;            // down rows per piece
-    static_assert((BN == 128 || BN == 256) && RH % NW == 0 && RD % NW == 0, "tile");
-    static_assert(NH >= 2 && NH <= 4 && (ND == NH || (NH == 2 && ND == 3)), "stages");
-    typedef typename Mfma<ET>::vec8 vec8;
-    __shared__ __align__(1024) char h0[RH * 1024];
-    __shared__ __align__(1024) char h1[RH * 1024];
-    __shared__ __align__(1024) char h2[NH > 2 ? RH * 1024 : 16];
-    __shared__ __align__(1024) char h3[NH > 3 ? RH * 1024 : 16];
-    __shared__ __align__(1024) char d0[RD * 1024];
-    __shared__ __align__(1024) char d1[RD * 1024];
-    __shared__ __align__(1024) char d2[ND > 2 ? RD * 1024 : 16];
-    __shared__ __align__(1024) char d3[ND > 3 ? RD * 1024 : 16];
-
-    int tm, sc;
-    if (!xcd_tile((int)blockIdx.x, ntm, ntn * KS, tm, sc)) return;  // uniform
-    const int ks = __builtin_amdgcn_readfirstlane((int)((unsigned)sc / (unsigned)ntn));
-    const int ct = sc - ks * ntn;
-    const int nU = *ucount;
-    const int kper = __builtin_amdgcn_readfirstlane(
-        ((int)((unsigned)(nU + KS - 1) / (unsigned)KS) + kBK - 1) / kBK * kBK);
-    const int kb = ks * kper;
-    const int ke = kb + kper < nU ? kb + kper : nU;
-    const int64_t n0 = (int64_t)ct * BN;
-    const int64_t m0 = (int64_t)tm * BM;
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int nn = lane & 15;
-    const int g = lane >> 4;
-    const int wt = w % WT, ww = w / WT;
-
-    const __amdgpu_buffer_rsrc_t rh = make_rsrc(Hhi, B * Up * 2);
-    const __amdgpu_buffer_rsrc_t rl = make_rsrc(PL == 2 ? Hlo : Hhi, B * Up * 2);
-    const __amdgpu_buffer_rsrc_t rd = make_rsrc(dc, L * d * 2);
-    const __amdgpu_buffer_rsrc_t ru = make_rsrc(ulist, (int64_t)(ke > 0 ? ke : 0) * 4);
-    // H pieces as in GEMM1: row 8 p + lane / 8, chunk c at position c ^ (row % 8)
-    const int hc = (lane & 7) ^ (lane >> 3);
-    // (a token past the batch has an offset past the buffer: reads as zeros)
-    const int hoff = (int)(((m0 + 8 * w + (lane >> 3)) * Up + kb) * 2) + hc * 16;
-    const int hstep = (int)(8 * NW * Up * 2);  // from a wave's piece to its next
-    // Down pieces: kRpp rows of BN columns. The 32-byte unit u (16 columns) of row r is kept at
-    // unit u ^ f(r), f(r) = r % 4 + 4 (r / 8) mod the units of a row: the 8 (16) rows that a
-    // transposing read takes at once then lie in different banks.
-    constexpr int kF = kRow / 32 - 1;  // 7 or 15
-    // From a wave's piece to its next the row grows by kDR, which flips at most the top bit of
-    // f (256 columns: kX in the byte offset).
-    constexpr int kDR = NW * kRpp, kX = BN == 256 && kDR == 16 ? 256 : 0;
-    static_assert(BN == 256 ? kDR == 16 : kDR % 16 == 0, "row swizzle");
-    const int drow = w * kRpp + lane / (64 / kRpp);
-    const int dc0 = (lane % (64 / kRpp)) ^ ((((drow & 3) | ((drow >> 3) << 2)) & kF) << 1);
-    const int dcol = (int)(n0 * 2) + 16 * dc0;
-    const bool dok0 = n0 + 8 * dc0 < d, dok1 = n0 + 8 * (dc0 ^ (kX / 16)) < d;  // d % 8 == 0
-    // The slots of a step's down rows are read a step ahead of the rows' loads (a position past
-    // the chunk is out of the descriptor's range: reads as 0, not used).
-    auto load_ids = [&](int k, int32_t(&ids)[LD]) {
-#pragma unroll
-        for (int j = 0; j < LD; ++j)
-            ids[j] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                ru, (kb + k * kBK + drow + j * kDR) * 4, 0, 0);
-    };
-    int32_t nid[LD];  // of the step whose rows are loaded next
-    int doff[LD];
-    auto row_offsets = [&](int k, const int32_t(&ids)[LD]) {
-#pragma unroll
-        for (int j = 0; j < LD; ++j) {
-            // (no short circuits: each would be a branch)
-            const bool ok = (drow < ke - kb - k * kBK - j * kDR) & (j & 1 ? dok1 : dok0) &
-                            ((unsigned)ids[j] < (unsigned)L);
-            const int o = ids[j] * (int)(d * 2) + (j & 1 ? dcol ^ kX : dcol);
-            doff[j] = ok ? o : kOOB;
-        }
-    };
-    // loads of step k into stage s (H past the chunk reads as zeros, so that what its rows hold
-    // there does not matter)
-    auto load_h = [&](int k, char* s) {
-        const bool ok = 8 * hc < ke - kb - k * kBK;
-#pragma unroll
-        for (int j = 0; j < LH; ++j)
-            load_lds16(PL == 2 && j * NW >= BM / 8 ? rl : rh, s + (j * NW + w) * 1024,
-                       ok ? hoff + j % (BM / 8 / NW) * hstep : kOOB, k * 128);
-    };
-    auto load_d = [&](char* s) {  // at row_offsets()
-#pragma unroll
-        for (int j = 0; j < LD; ++j) load_lds16(rd, s + (j * NW + w) * 1024, doff[j], 0);
-    };
-
-    f32x4_t acc[FW][FT];
-#pragma unroll
-    for (int i = 0; i < FW; ++i)
-#pragma unroll
-        for (int j = 0; j < FT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    vec8 fh[2][PL][FT], fd[2][FW];
-    const int to = (wt * 16 * FT + nn) * 128;
-    const int c0 = (g ^ (nn & 7)) * 16, c1 = ((4 + g) ^ (nn & 7)) * 16;
-    // Down fragments: lane (nn, g) needs union positions 8 g .. 8 g + 7 of column nn of a
-    // 16-column unit; ds_read_b64_tr_b16 hands lane i of a 16-lane group element i % 4 of the
-    // 8-byte pieces addressed by lanes i / 4 + 4 q, so lane nn addresses position 8 g + nn / 4
-    // (and + 4), columns 4 (nn % 4) .. + 3 of the unit.
-    const int df = ((nn >> 2) | (g << 2)) & kF;  // f of the lane's rows, in every half
-    int dadr[FW];
-#pragma unroll
-    for (int i = 0; i < FW; ++i)
-        dadr[i] = (8 * g + (nn >> 2)) * kRow + (((ww * FW + i) ^ df) * 32) + (nn & 3) * 8;
-    auto tr = [&](const char* p) {
-        const s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) s16x4_t*)const_cast<char*>(p));
-        return __builtin_bit_cast(u32x2_t, v);
-    };
-    auto frags = [&](const char* sh, const char* sd, int h) {
-#pragma unroll
-        for (int i = 0; i < FW; ++i) {
-            const u32x2_t lo = tr(sd + dadr[i] + h * 32 * kRow);
-            const u32x2_t hi = tr(sd + dadr[i] + (h * 32 + 4) * kRow);
-            fd[h][i] = Mfma<ET>::vec(V16{{lo[0], lo[1], hi[0], hi[1]}});
-        }
-        const int c = h ? c1 : c0;
-#pragma unroll
-        for (int q = 0; q < PL; ++q)
-#pragma unroll
-            for (int j = 0; j < FT; ++j)
-                fh[h][q][j] = Mfma<ET>::vec(ld16(sh + q * BM * 128 + to + j * 2048 + c));
-    };
-    auto mults = [&](int h) {
-#pragma unroll
-        for (int q = 0; q < PL; ++q)
-#pragma unroll
-            for (int j = 0; j < FT; ++j)
-#pragma unroll
-                for (int i = 0; i < FW; ++i)
-                    acc[i][j] = Mfma<ET>::mma(fd[h][i], fh[h][q][j], acc[i][j]);
-    };
-    char* const hs[4] = {h0, h1, h2, h3};
-    char* const ds[4] = {d0, d1, d2, d3};
-    // A K step, as in GEMM1. The offsets of the next down loads are formed from their slots just
-    // before the barrier; the slots after those are then asked for, a step ahead of their use.
-    constexpr int NM = PL * FT * FW, NR = PL * FT + 2 * FW;
-    constexpr int LA = kSplit ? LD : 0, LB = LH + (kSplit ? 0 : LD);
-    auto step = [&](int k, int q) {
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (kSplit) load_d(ds[(q + ND - 1) % ND]);
-        frags(hs[q % NH], ds[q % ND], 1);
-        mults(0);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            if (i < LA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, NM / NR, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        // the next step's loads have landed: at least these many were issued after them
-        wait_vm_lds<kSplit ? LD : (NH - 2) * (LH + LD)>();
-        row_offsets(k + ND, nid);
-        wg_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        load_ids(k + ND + 1, nid);
-        __builtin_amdgcn_sched_barrier(0);
-        load_h(k + NH, hs[q % NH]);
-        if constexpr (!kSplit) load_d(ds[q % ND]);
-        frags(hs[(q + 1) % NH], ds[(q + 1) % ND], 0);
-        mults(1);
-#pragma unroll
-        for (int i = 0; i < (NR > LB ? NR : LB); ++i) {
-            if (i < LB) {
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-            if (i < NR) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            }
-        }
-        asm volatile("" ::: "memory");
-    };
-    if (kb < ke) {
-        const int nk = (ke - kb + kBK - 1) / kBK;
-        int32_t pid[ND][LD];
-#pragma unroll
-        for (int q = 0; q < ND; ++q) load_ids(q, pid[q]);
-        load_ids(ND, nid);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < NH; ++q) {
-            row_offsets(q, pid[q]);
-            load_h(q, hs[q]);
-            load_d(ds[q]);
-            __builtin_amdgcn_sched_barrier(0);  // the counted waits rely on the stages' order
-        }
-        if constexpr (kSplit) row_offsets(ND - 1, pid[ND - 1]);  // step 0 loads these rows
-        wait_vm_lds<(NH - 1) * (LH + LD)>();
-        wg_barrier();
-        frags(h0, d0, 0);
-        int k = 0;
-        for (; k + kPer <= nk; k += kPer) {
-#pragma unroll
-            for (int q = 0; q < kPer; ++q) step(k + q, q);
-        }
-#pragma unroll
-        for (int q = 0; q < kPer - 1; ++q)
-            if (k + q < nk) step(k + q, q);
-        wait_vm_lds<0>();  // nothing may land in LDS once the work-group is gone
-    }
-
-    // element e of acc[i][j]: column n0 + 16 (ww FW + i) + 4 g + e of token
-    // m0 + 16 (wt FT + j) + nn
-    const int64_t nch = part_chunks(d);
-#pragma unroll
-    for (int j = 0; j < FT; ++j) {
-        const int64_t tok = m0 + 16 * (wt * FT + j) + nn;
-#pragma unroll
-        for (int i = 0; i < FW; ++i) {
-            const int64_t col = n0 + 16 * (ww * FW + i) + 4 * g;
-            if (tok < B && col < d) {
-                float* p = ks == 0 ? y + tok * d + col
-                                   : part + part_off(tok, ks - 1, col, KS - 1, nch);
-                *reinterpret_cast<f32x4_t*>(p) = acc[i][j];
-            }
-        }
-    }
-}
-
-// y += the P partials of chunks 1 .. KS - 1 (P = KS - 1), in order: one float4 of y a thread
-__global__ __launch_bounds__(256) void add_partials(const float* __restrict__ part, int P,
-                                                    int64_t n4, int64_t d, float* __restrict__ y) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n4) return;
-    const int64_t e = 4 * i;
-    const int64_t b = e / d, c = e - b * d;  // d % 8 == 0: the float4 is in one row
-    const f32x4_t* p = reinterpret_cast<const f32x4_t*>(part + part_off(b, 0, c, P, part_chunks(d)));
-    f32x4_t s = *reinterpret_cast<const f32x4_t*>(y + e);
-    int q = 0;
-    for (; q + 4 <= P; q += 4) {
-        f32x4_t v[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = p[(q + r) * (kChunk / 4)];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s += v[r];
-    }
-    for (; q < P; ++q) s += p[q * (kChunk / 4)];
-    *reinterpret_cast<f32x4_t*>(y + e) = s;
 }
 
 // ---- tile choice ---------------------------------------------------------------------------
@@ -918,7 +307,7 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
 #define SI_G1(BM, BN, WT, WW, NX, NWT)                                                                \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kUnion, BM, BN, WT, WW, NX, NWT>), g1, dim3(64 * WT * WW),  \
                           0, s, ev0, nullptr, 0, xx, B, d, gu, L, ulist, ucount, bits, p.W, hhi, \
-                          hlo, p.Up, p.ntm1, nullptr)
+                          hlo, p.Up, p.ntm1, nullptr, nullptr, 0)
     switch (p.g1) {
         case 0: SI_G1(256, 256, 2, 4, 2, 3); break;
         case 1: SI_G1(256, 160, 4, 2, 3, 3); break;
@@ -927,9 +316,9 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
 #undef SI_G1
     const dim3 g2((unsigned)((int64_t)p.ntm2 * p.ntn2 * p.KS + 7) / 8 * 8);
 #define SI_G2(PL, BM, BN, WT, WW, NH, ND)                                                            \
-    hipExtLaunchKernelGGL((gemm2_pipe<ET, PL, BM, BN, WT, WW, NH, ND>), g2, dim3(64 * WT * WW), 0, s, \
-                          nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, ulist, ucount, y, part,   \
-                          p.KS, p.ntm2, p.ntn2)
+    hipExtLaunchKernelGGL((gemm2_pipe<ET, true, PL, BM, BN, WT, WW, NH, ND>), g2,               \
+                          dim3(64 * WT * WW), 0, s, nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, \
+                          ulist, ucount, nullptr, (int64_t)0, y, part, p.KS, p.ntm2, p.ntn2)
     if (!fast)
         SI_G2(2, 128, 128, 4, 2, 3, 3);
     else if (p.g2 == 0)
@@ -961,7 +350,7 @@ hipError_t launch_activations_mfma_t(const void* x, int64_t T, int64_t d, const 
     hipExtLaunchKernelGGL((gemm1_pipe<ET, MODE, BM, BN, WT, WW, NX, NWT>),                           \
                           dim3((unsigned)(nst * ntm + 7) / 8 * 8), dim3(64 * WT * WW), 0, s, ev0, \
                           ev1, 0, xx, T, d, gu, L, nullptr, nullptr, nullptr, (int64_t)0,        \
-                          nullptr, nullptr, ldo, ntm, out)
+                          nullptr, nullptr, ldo, ntm, out, nullptr, 0)
 #define SI_ACT_TILES(MODE)                                                \
     switch (c) {                                                          \
         case 0: SI_ACT_LAUNCH(MODE, 256, 256, 2, 4, 2, 3); break;            \

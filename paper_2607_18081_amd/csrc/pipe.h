@@ -16,8 +16,18 @@ namespace si {
 typedef __attribute__((address_space(3))) void lds_void;
 
 // 16 bytes per lane from r at voff + soff to lds + 16 * lane (lds wave-uniform)
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, char* lds, int voff, int soff) {
+// (POL: the cache policy, kNonTemporal or 0)
+template <int POL = 0>
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, char* lds, int voff, int soff);
+template <>
+__device__ __forceinline__ void load_lds16<0>(__amdgpu_buffer_rsrc_t r, char* lds, int voff,
+                                              int soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds, 16, voff, soff, 0, 0);
+}
+template <>
+__device__ __forceinline__ void load_lds16<kNonTemporal>(__amdgpu_buffer_rsrc_t r, char* lds,
+                                                         int voff, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)lds, 16, voff, soff, 0, kNonTemporal);
 }
 
 // Waits until at most N of this wave's vector memory loads are outstanding and none of its LDS
@@ -38,7 +48,9 @@ SI_WAIT_VM(24) SI_WAIT_VM(25) SI_WAIT_VM(26) SI_WAIT_VM(27) SI_WAIT_VM(28) SI_WA
 SI_WAIT_VM(30) SI_WAIT_VM(31) SI_WAIT_VM(32) SI_WAIT_VM(33) SI_WAIT_VM(34) SI_WAIT_VM(35)
 SI_WAIT_VM(36) SI_WAIT_VM(37) SI_WAIT_VM(38) SI_WAIT_VM(39) SI_WAIT_VM(40) SI_WAIT_VM(41)
 SI_WAIT_VM(42) SI_WAIT_VM(43) SI_WAIT_VM(44) SI_WAIT_VM(45) SI_WAIT_VM(46) SI_WAIT_VM(47)
-SI_WAIT_VM(48)
+SI_WAIT_VM(48) SI_WAIT_VM(49) SI_WAIT_VM(50) SI_WAIT_VM(51) SI_WAIT_VM(52) SI_WAIT_VM(53)
+SI_WAIT_VM(54) SI_WAIT_VM(55) SI_WAIT_VM(56) SI_WAIT_VM(57) SI_WAIT_VM(58) SI_WAIT_VM(59)
+SI_WAIT_VM(60) SI_WAIT_VM(61) SI_WAIT_VM(62) SI_WAIT_VM(63)
 #undef SI_WAIT_VM
 
 // Barrier of the work-group's waves; memory operations do not move across it at compile time.

@@ -271,12 +271,55 @@ def test_union_tiled_tiles(B, L, d, step, dt):
     want = torch.where(mask, h, 0.0) @ dn.double()
     for flags, tol in ((0, 2.0 ** (-9 if dt == torch.bfloat16 else -12)),
                        (si.FLAG_EXACT_H, 1e-4)):
-        got = si.selective_ffn(x, off, idx, gu, dn, flags=flags)
+        # a workspace full of NaN bits: nothing that a call did not write may reach y
+        et = 2 if dt == torch.float16 else 1
+        ws = torch.full((si.selective_ffn_workspace(B, idx.numel(), L, d, et, et, flags),), 255,
+                        dtype=torch.uint8, device="cuda")
+        got = si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws)
         assert not got[3].any()
         err = ((got - want).norm() / want.norm()).item()
         say(f"  flags {flags}: {err:.2e}")
         assert err <= tol
-        assert torch.equal(got, si.selective_ffn(x, off, idx, gu, dn, flags=flags))
+        assert torch.equal(got, si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws))
+
+
+@pytest.mark.parametrize("B,L,d", [
+    # token tiles of 16, 32, 64 and 128 at their edges; slot tiles of 32, 40, 48 and 64 by the
+    # number of loaded slots; GEMM2 column tiles of 128 (d <= 2048 or 16 tokens) and 256
+    (5, 600, 520), (16, 9000, 136), (16, 11000, 72), (16, 16000, 264), (17, 8200, 2056),
+    (32, 11000, 200), (32, 13001, 64), (33, 8190, 2568), (64, 9677, 328), (64, 12280, 72),
+    (64, 15999, 136), (65, 8192, 448), (127, 10000, 2312), (127, 12000, 104), (127, 16383, 8)])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_union_word_tiles(B, L, d, dt):
+    """Every tile of the row-word GEMMs at ragged token, slot, column and K edges, against the
+    definition in float64 on the GPU: h as a hi + lo pair to 1e-4 as elsewhere, with FAST_H
+    rounded to one 16-bit value (2^-9 of each product in bf16, 2^-12 in half, at most)."""
+    say(f"word tiles B={B} L={L} d={d} {dt}")
+    g = torch.Generator(device="cuda").manual_seed(B + L + d)
+    r = lambda s, *sh: torch.empty(sh, device="cuda").normal_(0, s, generator=g).to(dt)
+    gu, dn, x = r(d ** -0.5, L, 2, d), r(d ** -0.5, L, d), r(1.0, B, d)
+    mask = torch.rand((B, L), device="cuda", generator=g) < 0.2
+    mask[:, L // 3: L // 2] = False                       # words that no token has
+    mask[3] = False                                       # an empty set
+    mask[B - 1, L - 1] = True
+    off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+    off[1:] = mask.sum(1).cumsum(0)
+    idx = torch.arange(L, device="cuda").expand(B, -1)[mask].to(torch.int32)
+    xx = x.double()
+    h = torch.nn.functional.silu(xx @ gu[:, 0].double().t()) * (xx @ gu[:, 1].double().t())
+    want = torch.where(mask, h, 0.0) @ dn.double()
+    for flags, tol in ((0, 1e-4),
+                       (si.FLAG_FAST_H, 2.0 ** (-9 if dt == torch.bfloat16 else -12))):
+        # a workspace full of NaN bits: nothing that a call did not write may reach y
+        et = 2 if dt == torch.float16 else 1
+        ws = torch.full((si.selective_ffn_workspace(B, idx.numel(), L, d, et, et, flags),), 255,
+                        dtype=torch.uint8, device="cuda")
+        got = si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws)
+        assert not got[3].any()
+        err = ((got - want).norm() / want.norm()).item()
+        say(f"  flags {flags}: {err:.2e}")
+        assert err <= tol
+        assert torch.equal(got, si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws))
 
 
 @pytest.mark.parametrize("seed", range(24))
