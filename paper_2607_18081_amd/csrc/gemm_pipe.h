@@ -17,6 +17,24 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
 constexpr int kBK = 64;  // K step (elements)
 
+// Position of the r-th (0-based) set bit of u; requires r < popcount(u).
+__device__ __forceinline__ int nth_set_bit(uint32_t u, int r) {
+    int pos = 0;
+#pragma unroll
+    for (int half = 16; half >= 1; half >>= 1) {
+        const uint32_t low = (1u << half) - 1u;
+        const int c = __popc(u & low);
+        if (r >= c) {
+            r -= c;
+            u >>= half;
+            pos += half;
+        } else {
+            u &= low;
+        }
+    }
+    return pos;
+}
+
 // Steps of a run, for sums of nk steps (2 MFMAs each) taken in runs whose results are then added
 // up: runs of m of n MFMAs leave a squared rounding error of about n (m + n / m) / 2, least at
 // m = sqrt(n). One run leaves n^2 / 2.
@@ -39,7 +57,10 @@ __device__ __forceinline__ void flush_sums(f32x4_t (&tot)[M][N], f32x4_t (&acc)[
 
 // ---- GEMM1 ---------------------------------------------------------------------------------
 // MODE selects what the epilogue produces (the product itself is the same):
-//   kUnion:  h masked by the token bitmaps, over the union list, as 16-bit hi (and lo) planes;
+//   kUnion:  h masked by the token bitmaps, over the union list, as 16-bit hi (and lo) planes.
+//            With nb = 0 the list is given. With nb > 0 it is formed here: part[0..nb) are
+//            bitmaps whose OR is the union (W <= kScanWords words), every work-group finds its
+//            own slots from them, and those of the first token tile write the list for GEMM2;
 //   kAct:    the activation of every slot (the union list is the identity, no mask), float32
 //            out[tok * Up + slot];
 //   kScore:  Eq. 1 for this work-group's tokens: sum over its BM tokens of |a| per slot, added
@@ -55,6 +76,9 @@ enum { kUnion = 0, kAct = 1, kScore = 2, kWord = 3 };
 // tokens' words lie in different banks)
 constexpr int kWin = 16, kWinP = kWin + 1;
 
+// Union words a GEMM1 work-group scans by itself (L <= 32768)
+constexpr int kScanWords = 1024;
+
 // BM tokens x BN weight rows (BN / 2 union slots); WT x WW waves of FT x FW 16x16 MFMA tiles,
 // the weight rows as the M operand, so a lane ends up with 4 consecutive weight rows of one
 // token. Those are 2 gate and 2 up rows of the same two slots, so SiLU * up needs no data
@@ -63,8 +87,8 @@ constexpr int kWin = 16, kWinP = kWin + 1;
 template <typename ET, int MODE, int BM, int BN, int WT, int WW, int NX, int NWT>
 __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     const uint16_t* __restrict__ x, int64_t B, int64_t d, const uint16_t* __restrict__ gu, int64_t L,
-    const int32_t* __restrict__ ulist, const int* __restrict__ ucount,
-    const uint32_t* __restrict__ bits, int64_t W, uint16_t* __restrict__ Hhi,
+    int32_t* __restrict__ ulist, int* __restrict__ ucount, const uint32_t* __restrict__ part,
+    int nb, const uint32_t* __restrict__ bits, int64_t W, uint16_t* __restrict__ Hhi,
     uint16_t* __restrict__ Hlo, int64_t Up, int ntm, float* __restrict__ out,
     uint32_t* __restrict__ words, int hi_only) {
     constexpr int NW = WT * WW, kThr = 64 * NW;
@@ -100,18 +124,76 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     __shared__ __align__(1024) char w6[NWT > 6 ? RW * 1024 : 16];
     __shared__ __align__(1024) char w7[NWT > 7 ? RW * 1024 : 16];
 
-    const int nU = MODE == kUnion ? *ucount : (int)L;
-    int tm, st;
-    // (kWord: the whole of the last word, so that GEMM2 finds H defined over every step)
-    const int nst = ((MODE == kWord ? (int)W * 32 : nU) + kS - 1) / kS;
-    if (!xcd_tile((int)blockIdx.x, ntm, nst, tm, st)) return;  // uniform
-    const int64_t m0 = (int64_t)tm * BM, u0 = (int64_t)st * kS;
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int nn = lane & 15;
     const int g = lane >> 4;
     const int wt = w % WT, ww = w / WT;
+
+    // kUnion with nb > 0: the union words and the union position of each word's first slot.
+    // (The tables lie in stages that are not loaded yet.)
+    int nU = (int)L;
+    int* const wpos = reinterpret_cast<int*>(x0);
+    uint32_t* const wtab = reinterpret_cast<uint32_t*>(x0) + kScanWords;
+    static_assert(MODE != kUnion || (kScanWords % kThr == 0 && 8 * kScanWords <= RX * 1024), "scan");
+    if constexpr (MODE == kUnion) {
+        if (nb > 0) {
+            // thread t: words kRun t .., 8 bitmaps' loads in flight
+            constexpr int kRun = kScanWords / kThr;
+            const __amdgpu_buffer_rsrc_t rp = make_rsrc(part, (int64_t)nb * W * 4);
+            uint32_t run_word[kRun];
+#pragma unroll
+            for (int i = 0; i < kRun; ++i) run_word[i] = 0u;
+            for (int r0 = 0; r0 < nb; r0 += 8) {
+                uint32_t v[kRun][8];
+#pragma unroll
+                for (int i = 0; i < kRun; ++i)
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        v[i][q] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                            rp,
+                            (r0 + q < nb) & (kRun * t + i < (int)W)
+                                ? ((r0 + q) * (int)W + kRun * t + i) * 4
+                                : kOOB,
+                            0, 0);
+#pragma unroll
+                for (int i = 0; i < kRun; ++i)
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) run_word[i] |= v[i][q];
+            }
+            // positions: a wave's counts scanned, then the waves'
+            int* const wtot = reinterpret_cast<int*>(x1);
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < kRun; ++i) c += __popc(run_word[i]);
+            const int incl = wave_incl_scan(c);
+            if (lane == kWave - 1) wtot[w] = incl;
+            __syncthreads();
+            nU = 0;
+            int pos = incl - c;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                pos += q < w ? wtot[q] : 0;
+                nU += wtot[q];
+            }
+#pragma unroll
+            for (int i = 0; i < kRun; ++i) {
+                wpos[kRun * t + i] = pos;
+                wtab[kRun * t + i] = run_word[i];
+                pos += __popc(run_word[i]);
+            }
+            nU = __builtin_amdgcn_readfirstlane(nU);
+            if (blockIdx.x == 0 && t == 0) *ucount = nU;
+        } else {
+            nU = *ucount;
+        }
+    }
+    // (kWord: the whole of the last word, so that GEMM2 finds H defined over every step)
+    const int nst = ((MODE == kWord ? (int)W * 32 : nU) + kS - 1) / kS;
+    int tm, st;
+    if (!xcd_tile((int)blockIdx.x, ntm, nst, tm, st)) return;  // uniform
+    const int64_t m0 = (int64_t)tm * BM, u0 = (int64_t)st * kS;
 
     const __amdgpu_buffer_rsrc_t rbm =
         make_rsrc(bits, MODE == kUnion || MODE == kWord ? B * W * 4 : 0);
@@ -144,15 +226,38 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
         if (t >= first && t < 2 && wd + t < W && 32 * t < wsh + kS)
             words[(int64_t)tm * W + wd + t] = (uint32_t)(uword >> (32 * t));
     }
-    // slot of union position u0 + p, -1 past the union
-    const __amdgpu_buffer_rsrc_t rul = make_rsrc(ulist, MODE == kUnion ? (int64_t)nU * 4 : 0);
-    auto union_slot = [&](int p) -> int32_t {
+    // kUnion: the tile's slots, -1 past the union, in a table for the row offsets; thread t
+    // keeps slot t for the epilogue
+    int32_t* const stab = reinterpret_cast<int32_t*>(w1);
+    int32_t my_slot = -1;
+    if constexpr (MODE == kUnion) {
+        static_assert(kS <= kThr, "slots");
+        if (nb > 0) {
+            // thread t finds union position u0 + t: the last word that starts at or before it,
+            // then the set bit of that rank
+            __syncthreads();
+            if (t < kS) {
+                const int u = (int)u0 + t;
+                int wd = 0;
+#pragma unroll
+                for (int s = kScanWords / 2; s >= 1; s >>= 1)
+                    if (wpos[wd + s] <= u) wd += s;
+                if (u < nU) my_slot = wd * 32 + nth_set_bit(wtab[wd], u - wpos[wd]);
+            }
+        } else if (t < kS && u0 + t < nU) {
+            const int32_t sl = ulist[u0 + t];
+            if ((unsigned)sl < (unsigned)L) my_slot = sl;
+        }
+        if (t < kS) stab[t] = my_slot;
+        __syncthreads();
+        if (nb > 0 && tm == 0 && t < kS && u0 + t < nU) ulist[u0 + t] = my_slot;
+    }
+    // slot of row pair p of the tile, -1: none
+    auto tile_slot = [&](int p) -> int32_t {
         const int u = (int)u0 + p;
-        int32_t sl = u;
-        if constexpr (MODE == kUnion)
-            sl = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rul, u * 4, 0, 0);
-        if constexpr (MODE == kWord) return ((uword >> (wsh + p)) & 1u) && u < nU ? sl : -1;
-        return (u < nU && (unsigned)sl < (unsigned)L) ? sl : -1;
+        if constexpr (MODE == kUnion) return p < kS ? stab[p] : -1;
+        if constexpr (MODE == kWord) return ((uword >> (wsh + p)) & 1u) && u < nU ? u : -1;
+        return u < nU ? u : -1;
     };
     // weight row 16 f + 4 q + e of the tile (e < 4): plane e / 2 (gate, up) of slot
     // slot_of(f, q, e % 2). A wave's tiles f come in pairs, over which a lane's slots are four
@@ -177,7 +282,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
 #pragma unroll
     for (int j = 0; j < LW + (kPart ? 1 : 0); ++j) {
         const int r = 8 * (j * NW + w) + (lane >> 3);  // (past the tile: not loaded)
-        const int32_t sl = union_slot(slot_of(r / 16, (r % 16) / 4, r & 1));
+        const int32_t sl = tile_slot(slot_of(r / 16, (r % 16) / 4, r & 1));
         woff[j] = sl >= 0 ? (int)(((int64_t)sl * 2 + ((r >> 1) & 1)) * d * 2) + cb : kOOB;
     }
     // the mask's window: kWin bitmap words from the first slot's on, unless the tile's slots
@@ -186,8 +291,9 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     bool in_win = false;
     if constexpr (MODE == kUnion) {
         const int last = (int)(nU - u0 < kS ? nU - u0 : kS) - 1;
-        win0 = __builtin_amdgcn_readfirstlane(ulist[u0] >> 5);
-        in_win = __builtin_amdgcn_readfirstlane(ulist[u0 + last] >> 5) - win0 < kWin;
+        win0 = __builtin_amdgcn_readfirstlane(stab[0] >> 5);
+        in_win = __builtin_amdgcn_readfirstlane(stab[last] >> 5) - win0 < kWin;
+        __syncthreads();  // the tables are done with: their stages may be loaded
     }
 
     const int nk = (int)((d + kBK - 1) / kBK);
@@ -342,8 +448,8 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     double* const ssum = reinterpret_cast<double*>(x0);          // kScore: sums per wave row
     static_assert(MODE != kUnion || BM * kWinP * 4 <= RX * 1024, "mask window");
     static_assert(MODE != kScore || WT * kS * 8 <= RX * 1024, "sums");
-    static_assert(kS <= kThr, "slots");
-    if (MODE != kWord && t < kS) sslot[t] = union_slot(t);
+    if (MODE == kUnion && t < kS) sslot[t] = my_slot;
+    if ((MODE == kAct || MODE == kScore) && t < kS) sslot[t] = tile_slot(t);
     if constexpr (MODE == kUnion) {
         if (in_win) {
             constexpr int kWinQ = BM * kWin / kThr;

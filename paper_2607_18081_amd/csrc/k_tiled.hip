@@ -165,6 +165,7 @@ struct TPlan {
     int g1, ntm1, nst;       // GEMM1: tile (kG1Tiles), token tiles, slot tiles (of all L slots)
     int g2, ntm2, ntn2, KS;  // GEMM2: tile (kG2Tiles), token tiles, column tiles, K chunks
     int64_t nb;              // blocks of 64 tokens
+    int scan;                // GEMM1 forms the union list itself
     size_t off_bits, off_words, off_ulist, off_count, off_hhi, off_hlo, off_part, total;
 };
 
@@ -201,7 +202,7 @@ TPlan make_tplan(int64_t B, int64_t L, int64_t d, int num_cu, bool exact) {
     for (int c = 0; c < (exact ? 1 : kG2Count); ++c) {
         const G2Tile& tl = exact ? kG2Exact : kG2Tiles[c];
         const int64_t tiles = cdiv(B, tl.bm) * cdiv(d, tl.bn);
-        for (int64_t ks = 1; ks <= rows + 1 && ks <= steps; ++ks) {
+        for (int64_t ks = 1; ks <= rows && ks <= steps; ++ks) {
             const double cost = (double)(cdiv(tiles * ks, num_cu) * cdiv(steps, ks) * tl.cost) +
                                 2e-4 * (double)(B * d) * (double)(ks - 1) + (ks > 1 ? 300. : 0.);
             if (cost < bc) bc = cost, p.g2 = c, p.KS = (int)ks;
@@ -213,6 +214,10 @@ TPlan make_tplan(int64_t B, int64_t L, int64_t d, int num_cu, bool exact) {
     size_t o = 0;
     p.off_bits = o;
     o = align256(o + (size_t)B * p.W * 4);
+    // Up to 2048 tokens and 32768 slots every GEMM1 work-group ORs the blocks and scans the
+    // union words in its prologue (about 1 us) instead of a launch of one work-group before it
+    // (8 us). More tokens would make its reads as long as that launch's.
+    p.scan = p.W <= kScanWords && B <= 2048;
     p.nb = (B + 63) / 64;
     p.off_words = o;
     o = align256(o + (size_t)p.nb * p.W * 4);
@@ -299,14 +304,16 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(or_blocks, dim3((unsigned)((p.W + 63) / 64), (unsigned)p.nb), dim3(256), 0,
                        s, bits, B, p.W, words);
-    hipLaunchKernelGGL(union_scan, dim3(1), dim3(1024), (unsigned)(p.W * 4), s, words, p.nb, p.W,
-                       ulist, ucount);
+    if (!p.scan)
+        hipLaunchKernelGGL(union_scan, dim3(1), dim3(1024), (unsigned)(p.W * 4), s, words, p.nb,
+                           p.W, ulist, ucount);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const int nb1 = p.scan ? (int)p.nb : 0;
     const dim3 g1((unsigned)((int64_t)p.nst * p.ntm1 + 7) / 8 * 8);
 #define SI_G1(BM, BN, WT, WW, NX, NWT)                                                                \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kUnion, BM, BN, WT, WW, NX, NWT>), g1, dim3(64 * WT * WW),  \
-                          0, s, ev0, nullptr, 0, xx, B, d, gu, L, ulist, ucount, bits, p.W, hhi, \
+                          0, s, ev0, nullptr, 0, xx, B, d, gu, L, ulist, ucount, words, nb1, bits, p.W, hhi, \
                           hlo, p.Up, p.ntm1, nullptr, nullptr, 0)
     switch (p.g1) {
         case 0: SI_G1(256, 256, 2, 4, 2, 3); break;
@@ -349,7 +356,7 @@ hipError_t launch_activations_mfma_t(const void* x, int64_t T, int64_t d, const 
 #define SI_ACT_LAUNCH(MODE, BM, BN, WT, WW, NX, NWT)                                                 \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, MODE, BM, BN, WT, WW, NX, NWT>),                           \
                           dim3((unsigned)(nst * ntm + 7) / 8 * 8), dim3(64 * WT * WW), 0, s, ev0, \
-                          ev1, 0, xx, T, d, gu, L, nullptr, nullptr, nullptr, (int64_t)0,        \
+                          ev1, 0, xx, T, d, gu, L, nullptr, nullptr, nullptr, 0, nullptr, (int64_t)0, \
                           nullptr, nullptr, ldo, ntm, out, nullptr, 0)
 #define SI_ACT_TILES(MODE)                                                \
     switch (c) {                                                          \

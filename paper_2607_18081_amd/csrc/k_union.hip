@@ -191,7 +191,7 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
 #define SI_G1(BM, BN, WT, WW, NX)                                                                \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kWord, BM, BN, WT, WW, NX, NX>), g1,                   \
                           dim3(64 * WT * WW), 0, s, ev0, nullptr, 0, xx, B, d, gu, L, nullptr,   \
-                          nullptr, bits, p.W, hhi, hlo, p.Up, p.ntm, nullptr, words, hi_only)
+                          nullptr, nullptr, 0, bits, p.W, hhi, hlo, p.Up, p.ntm, nullptr, words, hi_only)
 #define SI_G2(BM, BN, WT, WW, NH, ND)                                                            \
     hipExtLaunchKernelGGL((gemm2_pipe<ET, false, 2, BM, BN, WT, WW, NH, ND>), g2,           \
                           dim3(64 * WT * WW), 0, s, nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, \

@@ -246,7 +246,9 @@ def test_union_tiled_k_step_counts(d):
     # slots so far apart that a tile's mask words do not fit its LDS window
     (1100, 5300, 136, 7), (512, 5300, 72, 9), (130, 9000, 136, 40),
     # GEMM2's 256 x 256 tile and split K, a ragged last column tile
-    (2048, 5500, 4088, 1)])
+    (2048, 5500, 4088, 1),
+    # the union list from its own kernel (many tokens, many slots), and the largest GEMM1 scans
+    (2060, 700, 72, 1), (128, 33000, 64, 1), (131, 32768, 64, 3)])
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
 def test_union_tiled_tiles(B, L, d, step, dt):
     """Every tile of the tiled GEMMs at ragged token, slot, column and K edges, against the
