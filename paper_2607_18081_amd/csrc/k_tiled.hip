@@ -142,9 +142,11 @@ constexpr int kG1Count = 3;
 struct G2Tile {
     int bm, bn, cost;
 };
-constexpr G2Tile kG2Tiles[] = {{256, 256, 143}, {256, 128, 95}, {128, 128, 55}};  // one 16-bit h
+constexpr G2Tile kG2Tiles[] = {{256, 256, 160}, {256, 128, 90}, {128, 128, 52}};  // one 16-bit h
 constexpr int kG2Count = 3;
-constexpr G2Tile kG2Exact = {128, 128, 85};  // hi + lo pair
+// (128 x 256 against 128 x 128, 200 tokens, d = 4096: 34 / 40 us, rows from HBM 44 / 56 us)
+constexpr G2Tile kG2Exact[] = {{128, 256, 190}, {128, 128, 116}};  // hi + lo pair
+constexpr int kG2ExactCount = 2;
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -199,16 +201,19 @@ TPlan make_tplan(int64_t B, int64_t L, int64_t d, int num_cu, bool exact) {
     const int64_t rows = partial_rows(B, L, d, num_cu);
     const int64_t steps = cdiv(L, kBK);
     double bc = 1e300;
-    for (int c = 0; c < (exact ? 1 : kG2Count); ++c) {
-        const G2Tile& tl = exact ? kG2Exact : kG2Tiles[c];
+    for (int c = 0; c < (exact ? kG2ExactCount : kG2Count); ++c) {
+        const G2Tile& tl = exact ? kG2Exact[c] : kG2Tiles[c];
         const int64_t tiles = cdiv(B, tl.bm) * cdiv(d, tl.bn);
-        for (int64_t ks = 1; ks <= rows && ks <= steps; ++ks) {
+        // (the pair's 256-column tile sums a chunk in one run, for want of registers: it is taken
+        // with short chunks only. 512 half tokens, d = 5120: 8.6e-7 from the 64-bit result in
+        // 3 such chunks, 7.1e-7 with 128 columns and runs)
+        for (int64_t ks = exact && c == 0 ? rows : 1; ks <= rows && ks <= steps; ++ks) {
             const double cost = (double)(cdiv(tiles * ks, num_cu) * cdiv(steps, ks) * tl.cost) +
                                 2e-4 * (double)(B * d) * (double)(ks - 1) + (ks > 1 ? 300. : 0.);
             if (cost < bc) bc = cost, p.g2 = c, p.KS = (int)ks;
         }
     }
-    const G2Tile& t2 = exact ? kG2Exact : kG2Tiles[p.g2];
+    const G2Tile& t2 = exact ? kG2Exact[p.g2] : kG2Tiles[p.g2];
     p.ntm2 = (int)cdiv(B, t2.bm);
     p.ntn2 = (int)cdiv(d, t2.bn);
     size_t o = 0;
@@ -326,12 +331,14 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
     hipExtLaunchKernelGGL((gemm2_pipe<ET, true, PL, BM, BN, WT, WW, NH, ND>), g2,               \
                           dim3(64 * WT * WW), 0, s, nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, \
                           ulist, ucount, nullptr, (int64_t)0, y, part, p.KS, p.ntm2, p.ntn2)
-    if (!fast)
+    if (!fast && p.g2 == 0)
+        SI_G2(2, 128, 256, 2, 4, 2, 3);
+    else if (!fast)
         SI_G2(2, 128, 128, 4, 2, 3, 3);
     else if (p.g2 == 0)
         SI_G2(1, 256, 256, 2, 4, 2, 3);
     else if (p.g2 == 1)
-        SI_G2(1, 256, 128, 4, 2, 3, 3);
+        SI_G2(1, 256, 128, 2, 4, 3, 3);
     else
         SI_G2(1, 128, 128, 2, 2, 4, 4);
 #undef SI_G2
