@@ -40,6 +40,18 @@ __device__ __forceinline__ uint32_t order_key(float v, int mode) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Lane 63: the largest of the wave's values (DPP row shifts, then two row broadcasts).
+__device__ __forceinline__ uint32_t wave_umax_last(uint32_t v) {
+    auto step = [&](uint32_t o) { v = o > v ? o : v; };
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));  // row_shr:1
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));  // row_shr:2
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));  // row_shr:4
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));  // row_shr:8
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));  // bcast:15
+    step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));  // bcast:31
+    return v;
+}
+
 // Exclusive prefix count of `flag` over the block in thread order; returns the prefix and
 // writes the block total to *total. Uses wave ballots and a scan of the 16 wave counts.
 __device__ __forceinline__ int block_prefix(bool flag, int* wave_cnt, int* total) {
@@ -157,23 +169,29 @@ struct TopkOut {
     int* ucount;
 };
 
+constexpr int kDigit = 11, kBins = 1 << kDigit;  // bits and bins of a pass
+constexpr int kOwn = kBins / kTopkThreads;       // bins a thread adds up
+constexpr int kHists = 4;                        // copies of the histogram, for the waves in turn
 constexpr int kMaxRegKeys = 32 * kTopkThreads;  // the register-resident kernel's longest row
 
-// vec: the rows are 16-byte aligned, so a thread's C keys are read as float4s.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 template <int C>
 __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __restrict__ scores,
                                                              int64_t L, int64_t ld, int64_t k,
-                                                             int mode, int vec, TopkOut o) {
+                                                             int mode, TopkOut o) {
     static_assert(32 % C == 0, "a thread's keys lie in one bitmap word");
-    constexpr int kStride = 257;  // one histogram per wave, a bank apart
     const int64_t b = blockIdx.x;
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int w = t >> 6;
-    __shared__ int hist[kTopkWaves * kStride];
-    __shared__ int tot[256];
+    __shared__ int hist[kHists][kBins + 1];  // copies a bank apart
     __shared__ int wave_tot[kTopkWaves];
-    __shared__ uint32_t s_or[kTopkWaves], s_and[kTopkWaves];
+    __shared__ uint32_t s_min[kTopkWaves], s_max[kTopkWaves];
+    __shared__ int s_digit, s_take, s_n;
+    __shared__ uint32_t s_key;
+    __shared__ uint32_t few[kWave];
+    __shared__ int n_few;
     __shared__ uint32_t jbits[kMaxRegKeys / 32];
     if (o.ulist) {  // the joined set as a bitmap
         for (int q = t; q < kMaxRegKeys / 32; q += kTopkThreads) jbits[q] = 0u;
@@ -189,15 +207,15 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
     uint32_t key[C];
     const int64_t rest = L - (int64_t)t * C;
     const int nvalid = rest <= 0 ? 0 : (rest < C ? (int)rest : C);
-    if (C % 4 == 0 && vec && nvalid == C) {
-        const float4* r4 = reinterpret_cast<const float4*>(row + (int64_t)t * C);
+    if (C % 4 == 0 && nvalid == C) {
+        // rows may begin at any float: 16-byte loads of 4-byte alignment (scalar loads of the
+        // lanes' runs of C keys took 3.4 us of a 7706-key row, these 1.2)
+        const f32x4_a4* r4 = reinterpret_cast<const f32x4_a4*>(row + (int64_t)t * C);
 #pragma unroll
         for (int q = 0; q < C / 4; ++q) {
-            const float4 v = r4[q];
-            key[4 * q] = order_key(v.x, mode);
-            key[4 * q + 1] = order_key(v.y, mode);
-            key[4 * q + 2] = order_key(v.z, mode);
-            key[4 * q + 3] = order_key(v.w, mode);
+            const f32x4_a4 v = r4[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) key[4 * q + e] = order_key(v[e], mode);
         }
     } else {
 #pragma unroll
@@ -209,52 +227,45 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
     uint32_t cand = k > 0 ? vmask : 0u;
     const uint32_t jw = (o.ulist && nvalid > 0) ? jbits[(t * C) / 32] >> ((t * C) & 31) : 0u;
     cand &= ~jw;
-    // bits common to every candidate need no pass: the search starts at the highest bit in
-    // which two candidates differ
-    uint32_t kor = 0u, kand = ~0u;
+    // least and largest candidate: the first digits cover just that range
+    uint32_t kmin = ~0u, kmax = 0u;
 #pragma unroll
     for (int j = 0; j < C; ++j)
         if ((cand >> j) & 1u) {
-            kor |= key[j];
-            kand &= key[j];
+            kmin = key[j] < kmin ? key[j] : kmin;
+            kmax = key[j] > kmax ? key[j] : kmax;
         }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        kor |= (uint32_t)__shfl_xor((int)kor, m, kWave);
-        kand &= (uint32_t)__shfl_xor((int)kand, m, kWave);
+    // (largest of ~kmin and of kmax over the wave: in lane 63)
+    const uint32_t wmin = ~wave_umax_last(~kmin), wmax = wave_umax_last(kmax);
+    if (lane == kWave - 1) {
+        s_min[w] = wmin;
+        s_max[w] = wmax;
     }
-    if (lane == 0) {
-        s_or[w] = kor;
-        s_and[w] = kand;
-    }
-    for (int q = t; q < kTopkWaves * kStride; q += kTopkThreads) hist[q] = 0;
+    for (int q = t; q < kHists * (kBins + 1); q += kTopkThreads) (&hist[0][0])[q] = 0;
+    if (t == 0) n_few = 0;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kTopkWaves; ++q) {
-        kor |= s_or[q];
-        kand &= s_and[q];
+        kmin = s_min[q] < kmin ? s_min[q] : kmin;
+        kmax = s_max[q] > kmax ? s_max[q] : kmax;
     }
-    const uint32_t diff = kor ^ kand;
-    const int top = diff ? 31 - __clz((int)diff) : -1;  // -1: all candidates equal (or none)
-    // the bits above `top`, decided before the first pass
-    uint32_t pmask = top < 0 ? ~0u : (top >= 31 ? 0u : ~((2u << top) - 1u));
-    uint32_t prefix = kand & pmask;
-    int* my_hist = hist + w * kStride;
-    int take = (int)k;   // how many still to take among the candidates matching the prefix
-    bool done = k == 0;  // every candidate matching the prefix is taken: no further pass
-#pragma unroll 1
-    for (int hi = top; hi >= 0 && !done; hi -= 8) {
-        // this pass decides bits lo .. hi (8 of them, fewer at the bottom)
-        const int lo = hi >= 7 ? hi - 7 : 0;
-        const uint32_t dmask = (1u << (hi - lo + 1)) - 1u;
-        // 1. count the candidates by digit into the wave's histogram; a run of equal digits
-        //    in a thread's keys is added at once (few distinct digits would serialise the
-        //    atomics on one bin)
+    // The k-th largest key T lies in [base, base + span]; a pass splits that into 2^11 bins of
+    // 2^shift keys. (No candidates at all: nothing is counted, and the first pass ends it.)
+    const uint32_t range = kmax - kmin;
+    const int width = range ? 32 - __clz((int)range) : 0;
+    int shift = width > kDigit ? width - kDigit : 0;
+    uint32_t base = kmin, span = ~0u;
+    int* const my_hist = hist[w % kHists];
+    int take = (int)k;   // how many still to take among the candidates in the range
+    bool done = k == 0;  // all of them are taken
+    while (!done) {
+        // 1. count the candidates by bin; a run of equal digits in a thread's keys is added at
+        //    once (few distinct digits would serialise the atomics on one bin)
         int cur = -1, cnt = 0;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            if (((cand >> j) & 1u) && (key[j] & pmask) == prefix) {
-                const int dg = (int)((key[j] >> lo) & dmask);
+            if (((cand >> j) & 1u) && key[j] - base <= span) {
+                const int dg = (int)((key[j] - base) >> shift);
                 if (dg != cur) {
                     if (cnt) atomicAdd(&my_hist[cur], cnt);
                     cur = dg;
@@ -265,59 +276,80 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
         }
         if (cnt) atomicAdd(&my_hist[cur], cnt);
         __syncthreads();
-        // 2. bins added in wave order; the histograms are cleared for the next pass
-        if (t < 256) {
-            int c = 0;
+        // 2. the copies added (and cleared for the next pass): thread t owns kOwn bins, the
+        //    largest digits in the lowest threads, and a block-wide scan counts the keys above
+        int c[kOwn], sum = 0;
 #pragma unroll
-            for (int q = 0; q < kTopkWaves; ++q) {
-                c += hist[q * kStride + t];
-                hist[q * kStride + t] = 0;
+        for (int e = 0; e < kOwn; ++e) {
+            const int bin = kBins - 1 - kOwn * t - e;
+            c[e] = 0;
+#pragma unroll
+            for (int q = 0; q < kHists; ++q) {
+                c[e] += hist[q][bin];
+                hist[q][bin] = 0;
             }
-            tot[t] = c;
+            sum += c[e];
         }
-        __syncthreads();
-        // 3. every wave finds the digit of the k-th key itself (the same result in each, so
-        //    no third barrier): lane l owns digits 255 - 4l .. 252 - 4l, `above` counts the
-        //    keys with a larger digit, exactly one digit qualifies. tot is rewritten only after
-        //    the next pass's first barrier, which every wave reaches after reading it.
-        int c4[4], sum = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            c4[e] = tot[255 - 4 * lane - e];
-            sum += c4[e];
-        }
-        int above = wave_incl_scan(sum) - sum;
-        int found = 0, dsel = 0, tsel = 0, dn = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (above < take && above + c4[e] >= take) {
-                found = 1;
-                dsel = 255 - 4 * lane - e;
-                tsel = take - above;
-                dn = tsel == c4[e];
-            }
-            above += c4[e];
-        }
-        const unsigned long long fm = __ballot(found);
-        if (fm == 0ull) {  // k above the number of candidates: every candidate is taken
+        int all;
+        int above = block_excl_scan(sum, wave_tot, &all);
+        if (all < take) {  // k above the number of candidates: every candidate is taken
+            base = 0u;
             done = true;
             break;
         }
-        const int src = __ffsll((long long)fm) - 1;
-        prefix |= (uint32_t)__builtin_amdgcn_readlane(dsel, src) << lo;
-        take = __builtin_amdgcn_readlane(tsel, src);
-        done = __builtin_amdgcn_readlane(dn, src) != 0;
-        pmask |= dmask << lo;
-    }
-    // keys compare on the bits decided
-    const uint32_t T = prefix;
+        // 3. exactly one bin holds the key of the wanted rank
 #pragma unroll
-    for (int j = 0; j < C; ++j) key[j] &= pmask;
+        for (int e = 0; e < kOwn; ++e) {
+            if (above < take && above + c[e] >= take) {
+                s_digit = kBins - 1 - kOwn * t - e;
+                s_take = take - above;
+                s_n = c[e];
+            }
+            above += c[e];
+        }
+        __syncthreads();
+        base += (uint32_t)s_digit << shift;
+        span = (1u << shift) - 1u;
+        take = s_take;
+        const int n = s_n;  // candidates in the bin
+        done = take == n;
+        if (done || shift == 0) break;
+        shift = shift > kDigit ? shift - kDigit : 0;
+        if (n > kWave) continue;
+        // 4. no more candidates than lanes: they are gathered, one a lane, and one wave ranks
+        //    them by comparing each with all (all 16 waves at it take 1 us longer)
+#pragma unroll
+        for (int j = 0; j < C; ++j)
+            if (((cand >> j) & 1u) && key[j] - base <= span) few[atomicAdd(&n_few, 1)] = key[j];
+        __syncthreads();
+        if (w == 0) {
+            const uint32_t mine = lane < n ? few[lane] : 0u;
+            int gt = 0, ge = 0;
+            for (int i = 0; i < n; ++i) {
+                const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+                gt += other > mine ? 1 : 0;
+                ge += other >= mine ? 1 : 0;
+            }
+            // a lane that holds the k-th key
+            const unsigned long long hit = __ballot(lane < n && gt < take && take <= ge);
+            if (lane == __ffsll((long long)hit) - 1) {
+                s_key = mine;
+                s_take = take - gt;
+                s_n = ge - gt;
+            }
+        }
+        __syncthreads();
+        base = s_key;
+        take = s_take;
+        done = take == s_n;
+        break;
+    }
+    const uint32_t T = base;
     uint32_t sel = 0u;  // bit j: key t*C + j is chosen
-    if (done) {  // every candidate equal to T is taken
+    if (done) {  // every candidate from T on is taken
 #pragma unroll
         for (int j = 0; j < C; ++j) sel |= (((cand >> j) & 1u) && key[j] >= T) ? 1u << j : 0u;
-    } else {  // the first `take` candidates equal to T in index order
+    } else {  // those above T, and the first `take` candidates equal to T in index order
         int n_eq = 0;
 #pragma unroll
         for (int j = 0; j < C; ++j) n_eq += (((cand >> j) & 1u) && key[j] == T) ? 1 : 0;
@@ -367,10 +399,8 @@ namespace {
 template <int C>
 void launch_reg_c(const float* scores, int64_t B, int64_t L, int64_t ld, int64_t k, int mode,
                   const TopkOut& o, hipStream_t s) {
-    const bool al = reinterpret_cast<uintptr_t>(scores) % 16 == 0;
-    const int vec = (al && (B <= 1 || ld % 4 == 0)) ? 1 : 0;
     hipLaunchKernelGGL(topk_rows_reg<C>, dim3((unsigned)B), dim3(kTopkThreads), 0, s, scores, L,
-                       ld, k, mode, vec, o);
+                       ld, k, mode, o);
 }
 
 // false when a row has more than 32768 keys
