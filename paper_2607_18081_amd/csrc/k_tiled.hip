@@ -132,13 +132,18 @@ __global__ __launch_bounds__(1024) void union_scan(const uint32_t* __restrict__ 
 
 // ---- tile choice ---------------------------------------------------------------------------
 // Time of one K step (64) of a work-group that has a CU to itself, in units of 10 ns, measured
-// over whole GEMMs (kernel time / rounds of work-groups / steps): the larger tile does more per
-// byte it takes in and per barrier, the smaller one fills the CUs where the product is small.
+// over whole GEMMs with the weights in HBM (kernel time / rounds of work-groups / steps): the
+// larger tile does more per byte it takes in and per barrier, the smaller one fills the CUs
+// where the product is small. By least (rounds x time) the choice was the fastest, or within 3%
+// of it, at each of 18 sizes from 128 to 2048 tokens; e.g. with 256 x 256, 256 x 192, 256 x 160,
+// 128 x 256 and 128 x 160 tiles 512 tokens x 11000 slots, d = 5120 take 114, 104, 172, 156 and
+// 180 us, 512 x 7706, d = 4096 85, 76, 69, 65 and 100, 200 x 8602, d = 4096 85, 77, 67, 63 and 51.
 struct G1Tile {
     int bm, bn, cost;
 };
-constexpr G1Tile kG1Tiles[] = {{256, 256, 143}, {256, 160, 103}, {128, 160, 56}};
-constexpr int kG1Count = 3;
+constexpr G1Tile kG1Tiles[] = {
+    {256, 256, 145}, {256, 192, 128}, {256, 160, 115}, {128, 256, 105}, {128, 160, 82}};
+constexpr int kG1Count = 5;
 struct G2Tile {
     int bm, bn, cost;
 };
@@ -322,7 +327,9 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
                           hlo, p.Up, p.ntm1, nullptr, nullptr, 0)
     switch (p.g1) {
         case 0: SI_G1(256, 256, 2, 4, 2, 3); break;
-        case 1: SI_G1(256, 160, 4, 2, 3, 3); break;
+        case 1: SI_G1(256, 192, 2, 4, 2, 3); break;
+        case 2: SI_G1(256, 160, 4, 2, 3, 3); break;
+        case 3: SI_G1(128, 256, 2, 4, 3, 3); break;
         default: SI_G1(128, 160, 2, 2, 4, 4); break;
     }
 #undef SI_G1
@@ -368,7 +375,9 @@ hipError_t launch_activations_mfma_t(const void* x, int64_t T, int64_t d, const 
 #define SI_ACT_TILES(MODE)                                                \
     switch (c) {                                                          \
         case 0: SI_ACT_LAUNCH(MODE, 256, 256, 2, 4, 2, 3); break;            \
-        case 1: SI_ACT_LAUNCH(MODE, 256, 160, 4, 2, 3, 3); break;            \
+        case 1: SI_ACT_LAUNCH(MODE, 256, 192, 2, 4, 2, 3); break;            \
+        case 2: SI_ACT_LAUNCH(MODE, 256, 160, 4, 2, 3, 3); break;            \
+        case 3: SI_ACT_LAUNCH(MODE, 128, 256, 2, 4, 3, 3); break;            \
         default: SI_ACT_LAUNCH(MODE, 128, 160, 2, 2, 4, 4); break;           \
     }
     if (score) {

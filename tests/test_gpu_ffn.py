@@ -238,8 +238,10 @@ def test_union_tiled_k_step_counts(d):
 
 
 @pytest.mark.parametrize("B,L,d,step", [
-    # GEMM1 tiles (tokens x weight rows) by what fills the CUs: 128 x 160, 256 x 160, 256 x 256
-    (130, 1290, 8, 1), (512, 5300, 72, 1), (1100, 5300, 136, 1),
+    # GEMM1 tiles (tokens x weight rows) by what fills the CUs: 128 x 160, 128 x 256, 256 x 160,
+    # 256 x 192, 256 x 256
+    (130, 1290, 8, 1), (512, 5300, 72, 1), (500, 9001, 72, 1), (600, 7300, 200, 1),
+    (1100, 5300, 136, 1), (600, 7300, 328, 1), (500, 9001, 520, 1),
     # K steps around one, two and three turns of the LDS stages, whole and ragged
     (512, 5300, 192, 1), (512, 5300, 264, 1), (1100, 5300, 384, 1), (1100, 5300, 456, 1),
     (1100, 5300, 832, 1), (200, 1290, 320, 1), (200, 1290, 520, 1),
