@@ -888,6 +888,58 @@ __global__ __launch_bounds__(256) void add_partials(const float* __restrict__ pa
         ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
+// The same with a wave per (token, 16 columns): lane l adds float4 l % 4 of partials l / 4,
+// l / 4 + 16, ..., the lanes meet in a fixed order.
+__global__ __launch_bounds__(256) void add_many_partials(const float* __restrict__ part, int P,
+                                                         int64_t pairs, int64_t nch, int64_t d,
+                                                         float* __restrict__ y) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t pair = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (pair >= pairs) return;
+    const int64_t b = pair / nch;
+    const int64_t c = (pair - b * nch) * kChunk + 4 * lane;
+    const bool mine = lane < kChunk / 4 && c < d;  // d % 8 == 0: the float4 is all in range
+    float* const py = y + b * d + c;
+    const f32x4_t* p = reinterpret_cast<const f32x4_t*>(part + pair * P * kChunk);
+    const int n4 = P * (kChunk / 4);
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+    if (mine) s = *reinterpret_cast<const f32x4_t*>(py);
+    for (int i = lane; i < n4; i += 4 * kWave) {
+        f32x4_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[q] = i + q * kWave < n4 ? p[i + q * kWave] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        s += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+#pragma unroll
+    for (int m = kChunk / 4; m < kWave; m <<= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] += __shfl_xor(s[e], m, kWave);
+    if (mine) *reinterpret_cast<f32x4_t*>(py) = s;
+}
+
+// Up to this many (token, 16 columns) pairs, and from 4 partials, a wave a pair: with few sums a
+// thread's chain of loads is the launch's time (whole call, 6000 slots, thread / wave a sum: 5
+// tokens, d = 256, 63 partials 23.2 / 13.4 us, 16 tokens, d = 4096, 7 partials 31.6 / 30.5; 33
+// tokens, d = 4096, 15 partials 45.0 / 43.3). With more, the waves' extra instructions are
+// (100 tokens, d = 5120, 11 partials 72.7 / 75.3 us, 300 tokens, d = 1024 45.5 / 46.9).
+constexpr int64_t kManyPairs = 10240;
+constexpr int kManyPartials = 4;
+// y += the P partials of B x d sums
+inline hipError_t launch_add_partials(const float* part, int P, int64_t B, int64_t d, float* y,
+                                      hipStream_t s) {
+    const int64_t nch = part_chunks(d), pairs = B * nch;
+    if (P >= kManyPartials && pairs <= kManyPairs) {
+        hipLaunchKernelGGL(add_many_partials, dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s,
+                           part, P, pairs, nch, d, y);
+    } else if (P > 0) {
+        const int64_t n4 = B * d / 4;
+        hipLaunchKernelGGL(add_partials, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, part,
+                           P, n4, d, y);
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 }  // namespace si

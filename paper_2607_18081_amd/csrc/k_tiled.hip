@@ -349,12 +349,7 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
     else
         SI_G2(1, 128, 128, 2, 2, 4, 4);
 #undef SI_G2
-    if (p.KS > 1) {
-        const int64_t n4 = B * d / 4;
-        hipLaunchKernelGGL(add_partials, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, part,
-                           p.KS - 1, n4, d, y);
-    }
-    return hipGetLastError();
+    return launch_add_partials(part, p.KS - 1, B, d, y, s);
 }
 
 template <typename ET>

@@ -1,0 +1,70 @@
+"""The union path at the edges of its dispatch rules, against the definition in float64.
+
+h travels as a hi + lo pair of 16-bit values below 128 tokens and with SI_FLAG_EXACT_H, held to
+1e-4 as elsewhere; as one 16-bit value with SI_FLAG_FAST_H and by default from 128 tokens, where
+rounding it leaves 2^-9 (bf16) or 2^-12 (half) of each product at most."""
+import pytest
+import torch
+
+import paper_2607_18081_amd as si
+from tests.gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+BF16, F16 = torch.bfloat16, torch.float16
+ONE_H = {BF16: 2.0 ** -9, F16: 2.0 ** -12}
+
+
+def problem(B, L, d, dt=BF16, density=0.2, seed=0, pool=None):
+    """A layer, activations and active sets (slots of `pool` only, when given; token 3 has none),
+    with the float64 result."""
+    g = torch.Generator(device="cuda").manual_seed(B + L + d + seed)
+    r = lambda s, *sh: torch.empty(sh, device="cuda").normal_(0, s, generator=g).to(dt)
+    gu, dn, x = r(d ** -0.5, L, 2, d), r(d ** -0.5, L, d), r(1.0, B, d)
+    mask = torch.rand((B, L), device="cuda", generator=g) < density
+    if pool is not None:
+        inside = torch.zeros(L, dtype=torch.bool, device="cuda")
+        inside[pool] = True
+        mask &= inside
+    mask[3] = False
+    off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+    off[1:] = mask.sum(1).cumsum(0)
+    idx = torch.arange(L, device="cuda").expand(B, -1)[mask].to(torch.int32)
+    cols = mask.any(0).nonzero().flatten()                # (the union: no other slot adds to y)
+    xx = x.double()
+    h = torch.nn.functional.silu(xx @ gu[cols, 0].double().t()) * (xx @ gu[cols, 1].double().t())
+    want = torch.where(mask[:, cols], h, 0.0) @ dn[cols].double()
+    return x, off, idx, gu, dn, want
+
+
+def call(x, off, idx, gu, dn, flags=0):
+    """One call with a workspace full of NaN bits: nothing that it did not write may reach y."""
+    et = 2 if x.dtype == F16 else 1
+    need = si.selective_ffn_workspace(x.shape[0], idx.numel(), gu.shape[0], x.shape[1], et, et,
+                                      flags)
+    ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+    return si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws)
+
+
+def rel(got, want):
+    return ((got - want).norm() / want.norm()).item()
+
+
+@pytest.mark.parametrize("B,L,d", [
+    # K chunks: 64 and as many as there are steps; 16, 8, 4 and 3 (at most 3 partials)
+    (5, 6000, 8), (5, 600, 72), (16, 6000, 2048), (16, 3000, 4096), (7, 700, 8192),
+    (6, 400, 10248),
+    # (token, 16 columns) pairs up to the wave-a-pair form's last and past it
+    (64, 6000, 2560), (64, 6000, 2568), (80, 3000, 2048), (81, 3000, 2048),
+    # the same from 128 tokens
+    (130, 4000, 128), (160, 3000, 1024), (161, 3000, 1024)])
+@pytest.mark.parametrize("flags", [0, si.FLAG_EXACT_H])
+def test_sums_of_the_k_chunks(B, L, d, flags):
+    say(f"partials B={B} L={L} d={d} flags {flags}")
+    p = problem(B, L, d)
+    got = call(*p[:5], flags=flags)
+    assert not got[3].any()
+    err = rel(got, p[5])
+    say(f"  {err:.2e}")
+    assert err <= (ONE_H[BF16] if B >= 128 and not flags else 1e-4)
+    assert torch.equal(got, call(*p[:5], flags=flags))
