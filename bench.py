@@ -494,7 +494,7 @@ def parity_from_oracle(work, outputs, tol):
             continue
         n = np.linalg.norm(want)
         err = float(np.linalg.norm(y[t] - want) / n) if n > 0 else float(np.linalg.norm(y[t]))
-        worst = max(worst, err)
+        worst = max(worst, err if err == err else float("inf"))  # (max() passes over a NaN)
     rec = {"tokens_checked": len(outputs), "max_rel_l2": worst, "tol": tol}
     if cfg.layers > 1:
         # free-running through the stack: reported for information, not held to a bound

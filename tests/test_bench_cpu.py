@@ -41,3 +41,10 @@ def test_parity_sees_a_wrong_token():
     outputs = {t: work.want[t].astype(np.float64) for t in range(B * STEPS)}
     outputs[7] = outputs[7] * 1.5
     assert bench.parity_from_oracle(work, outputs, 1e-5)["max_rel_l2"] > 0.3
+
+
+def test_parity_sees_a_nan():
+    work = Work()
+    outputs = {t: work.want[t].astype(np.float64) for t in range(B * STEPS)}
+    work.want[4, 1] = np.nan                              # what the launch writes
+    assert not bench.parity_from_oracle(work, outputs, 1e-5)["max_rel_l2"] <= 1e-5
