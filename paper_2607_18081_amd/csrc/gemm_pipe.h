@@ -68,8 +68,7 @@ __device__ __forceinline__ void flush_sums(f32x4_t (&tot)[M][N], f32x4_t (&acc)[
 //            host-side reducer adds the rows in order);
 //   kWord:   as kUnion, but without a union list: a slot tile is BN / 2 consecutive slots, H is
 //            indexed by slot, and rows that no token of the tile has are not loaded. The tile's
-//            union words go to words[tm * W ..] for GEMM2. The lo plane is always there, zero
-//            with hi_only (SI_FLAG_FAST_H).
+//            union words go to words[tm * W ..] for GEMM2.
 enum { kUnion = 0, kAct = 1, kScore = 2, kWord = 3 };
 
 // Token bitmap words a work-group keeps in LDS for the mask (per token; pitch odd so that 16
@@ -90,7 +89,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     int32_t* __restrict__ ulist, int* __restrict__ ucount, const uint32_t* __restrict__ part,
     int nb, const uint32_t* __restrict__ bits, int64_t W, uint16_t* __restrict__ Hhi,
     uint16_t* __restrict__ Hlo, int64_t Up, int ntm, float* __restrict__ out,
-    uint32_t* __restrict__ words, int hi_only) {
+    uint32_t* __restrict__ words) {
     constexpr int NW = WT * WW, kThr = 64 * NW;
     constexpr int FT = BM / (16 * WT), FW = BN / (16 * WW);
     constexpr int kS = BN / 2;
@@ -552,7 +551,6 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
                         h[e] = act ? h[e] : 0.0f;
                         hb[e] = Mfma<ET>::rne(h[e]);
                         lb[e] = Mfma<ET>::rne(h[e] - Mfma<ET>::widen(hb[e]));
-                        if (MODE == kWord && hi_only) lb[e] = 0u;
                     }
                     // up to the end of this tile, so that the 8-wide chunk of GEMM2 that
                     // straddles the union's end holds zeros past it (Up is a multiple of 64)
@@ -560,7 +558,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
                         uint32_t* ph = reinterpret_cast<uint32_t*>(Hhi + tok * Up + u);
 #pragma unroll
                         for (int e = 0; e < np; ++e) ph[e] = hb[2 * e] | (hb[2 * e + 1] << 16);
-                        if (Hlo) {  // the lo plane exists only for SI_FLAG_EXACT_H
+                        if (Hlo) {  // with the hi + lo pair only
                             uint32_t* pl = reinterpret_cast<uint32_t*>(Hlo + tok * Up + u);
 #pragma unroll
                             for (int e = 0; e < np; ++e) pl[e] = lb[2 * e] | (lb[2 * e + 1] << 16);
@@ -591,8 +589,10 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     float* __restrict__ y, float* __restrict__ part, int KS, int ntm, int ntn) {
     constexpr int NW = WT * WW;
     constexpr int FT = BM / (16 * WT), FW = BN / (16 * WW);
-    // 1 KB pieces of a stage and how many of them a wave loads
-    constexpr int RH = PL * BM / 8, RD = BN / 8, LH = RH / NW, LD = RD / NW;
+    // 1 KB pieces of a stage (of H one a wave at least; those past its rows stay zero) and how
+    // many of them a wave loads
+    constexpr int RHP = PL * BM / 8, RH = RHP < NW ? NW : RHP, RD = BN / 8;
+    constexpr int LH = RH / NW, LD = RD / NW;
     constexpr bool kSplit = ND > NH;
     constexpr int kPer = kSplit ? NH * ND : NH;  // steps after which the stages come round
     constexpr int kRow = 2 * BN;                 // bytes of a down row segment
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     constexpr int HP = BM / 8;
     static_assert(HP % NW == 0 || RH == NW, "H pieces");
     const int hw = HP < NW ? w % HP : w;
-    const uint16_t* const hfirst = HP < NW && w >= HP ? Hlo : Hhi;
+    const uint16_t* const hfirst = PL == 2 && HP < NW && w >= HP ? Hlo : Hhi;
     const __amdgpu_buffer_rsrc_t rh = make_rsrc(hfirst + m0 * Up, hbytes);
     const __amdgpu_buffer_rsrc_t rl = make_rsrc((PL == 2 ? Hlo : Hhi) + m0 * Up, hbytes);
     const __amdgpu_buffer_rsrc_t rd = make_rsrc(dc, L * d * 2);
@@ -650,7 +650,9 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     // H pieces as in GEMM1: row 8 p + lane / 8, chunk c at position c ^ (row % 8)
     // (a token past the batch has an offset past the buffer: reads as zeros)
     const int hc = (lane & 7) ^ (lane >> 3);
-    const int hoff = (int)(((8 * hw + (lane >> 3)) * Up + kb) * 2) + hc * 16;
+    const int hoff = RHP < NW && w >= RHP
+                         ? kOOB
+                         : (int)(((8 * hw + (lane >> 3)) * Up + kb) * 2) + hc * 16;
     const int hstep = (int)(8 * NW * Up * 2);  // from a wave's piece to its next
     // Down pieces: kRpp rows of BN columns. The 32-byte unit u (16 columns) of row r is kept at
     // unit u ^ f(r), f(r) = r % 4 + 4 (r / 8) mod the units of a row: the 8 (16) rows that a

@@ -324,7 +324,7 @@ hipError_t launch_union_tiled_t(const void* x, int64_t B, int64_t d, const int32
 #define SI_G1(BM, BN, WT, WW, NX, NWT)                                                                \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kUnion, BM, BN, WT, WW, NX, NWT>), g1, dim3(64 * WT * WW),  \
                           0, s, ev0, nullptr, 0, xx, B, d, gu, L, ulist, ucount, words, nb1, bits, p.W, hhi, \
-                          hlo, p.Up, p.ntm1, nullptr, nullptr, 0)
+                          hlo, p.Up, p.ntm1, nullptr, nullptr)
     switch (p.g1) {
         case 0: SI_G1(256, 256, 2, 4, 2, 3); break;
         case 1: SI_G1(256, 192, 2, 4, 2, 3); break;
@@ -366,7 +366,7 @@ hipError_t launch_activations_mfma_t(const void* x, int64_t T, int64_t d, const 
     hipExtLaunchKernelGGL((gemm1_pipe<ET, MODE, BM, BN, WT, WW, NX, NWT>),                           \
                           dim3((unsigned)(nst * ntm + 7) / 8 * 8), dim3(64 * WT * WW), 0, s, ev0, \
                           ev1, 0, xx, T, d, gu, L, nullptr, nullptr, nullptr, 0, nullptr, (int64_t)0, \
-                          nullptr, nullptr, ldo, ntm, out, nullptr, 0)
+                          nullptr, nullptr, ldo, ntm, out, nullptr)
 #define SI_ACT_TILES(MODE)                                                \
     switch (c) {                                                          \
         case 0: SI_ACT_LAUNCH(MODE, 256, 256, 2, 4, 2, 3); break;            \

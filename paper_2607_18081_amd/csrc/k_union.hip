@@ -177,12 +177,12 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
     uint32_t* bits = reinterpret_cast<uint32_t*>(base + p.off_bits);
     uint32_t* words = reinterpret_cast<uint32_t*>(base + p.off_words);
     uint16_t* hhi = reinterpret_cast<uint16_t*>(base + p.off_hhi);
-    uint16_t* hlo = reinterpret_cast<uint16_t*>(base + p.off_hlo);
+    const bool fast = (flags & SI_FLAG_FAST_H) != 0;  // h as one 16-bit value: no lo plane
+    uint16_t* hlo = fast ? nullptr : reinterpret_cast<uint16_t*>(base + p.off_hlo);
     float* part = reinterpret_cast<float*>(base + p.off_part);
     const uint16_t* xx = static_cast<const uint16_t*>(x);
     const uint16_t* gu = static_cast<const uint16_t*>(gate_up_c);
     const uint16_t* dc = static_cast<const uint16_t*>(down_c);
-    const int hi_only = (flags & SI_FLAG_FAST_H) != 0;
 
     hipError_t e = launch_token_bitmaps(offsets, idx, nnz, B, L, p.W, bits, s);
     if (e != hipSuccess) return e;
@@ -191,11 +191,13 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
 #define SI_G1(BM, BN, WT, WW, NX)                                                                \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kWord, BM, BN, WT, WW, NX, NX>), g1,                   \
                           dim3(64 * WT * WW), 0, s, ev0, nullptr, 0, xx, B, d, gu, L, nullptr,   \
-                          nullptr, nullptr, 0, bits, p.W, hhi, hlo, p.Up, p.ntm, nullptr, words, hi_only)
-#define SI_G2(BM, BN, WT, WW, NH, ND)                                                            \
-    hipExtLaunchKernelGGL((gemm2_pipe<ET, false, 2, BM, BN, WT, WW, NH, ND>), g2,           \
+                          nullptr, nullptr, 0, bits, p.W, hhi, hlo, p.Up, p.ntm, nullptr, words)
+#define SI_G2_PL(PL, BM, BN, WT, WW, NH, ND)                                                     \
+    hipExtLaunchKernelGGL((gemm2_pipe<ET, false, PL, BM, BN, WT, WW, NH, ND>), g2,               \
                           dim3(64 * WT * WW), 0, s, nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, \
                           nullptr, nullptr, words, p.W, y, part, p.KS, p.ntm, p.ntn)
+#define SI_G2(BM, BN, WT, WW, NH, ND)                                                            \
+    if (fast) SI_G2_PL(1, BM, BN, WT, WW, NH, ND); else SI_G2_PL(2, BM, BN, WT, WW, NH, ND)
     switch (p.bm * 1000 + p.bn1) {
         case 16064: SI_G1(16, 64, 1, 2, 8); break;
         case 16080: SI_G1(16, 80, 1, 1, 5); break;
@@ -225,6 +227,7 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
     }
 #undef SI_G1
 #undef SI_G2
+#undef SI_G2_PL
     return launch_add_partials(part, p.KS - 1, B, d, y, s);
 }
 

@@ -68,3 +68,39 @@ def test_sums_of_the_k_chunks(B, L, d, flags):
     say(f"  {err:.2e}")
     assert err <= (ONE_H[BF16] if B >= 128 and not flags else 1e-4)
     assert torch.equal(got, call(*p[:5], flags=flags))
+
+
+@pytest.mark.parametrize("B,d", [(5, 520), (17, 264), (33, 2568), (70, 2568), (100, 520)])
+@pytest.mark.parametrize("dt", [BF16, F16])
+def test_fast_h_is_one_value(B, d, dt):
+    """SI_FLAG_FAST_H: h is its 16-bit rounding alone. With the pair, its low half (zero, or of
+    the other sign) times an infinite down weight would make a NaN."""
+    L, s, c = 700, 301, 7
+    say(f"FAST_H B={B} d={d} {dt}")
+    x, off, idx, gu, dn, _ = problem(B, L, d, dt)
+    dn[s, c] = float("inf")
+    k = 20                                                # every token has slot s
+    idx = torch.cat([torch.randperm(L - 310, device="cuda")[:k - 1].add(310).sort().values if i
+                     else torch.tensor([s], device="cuda") for b in range(B) for i in (0, 1)])
+    off = torch.arange(0, (B + 1) * k, k, dtype=torch.int32, device="cuda")
+    got = call(x, off, idx.to(torch.int32), gu, dn, si.FLAG_FAST_H)
+    h = torch.nn.functional.silu(x.double() @ gu[s, 0].double()) * (x.double() @ gu[s, 1].double())
+    assert torch.equal(got[:, c], h.sign().float() * float("inf"))
+    got[:, c] = 0
+    assert got.isfinite().all()
+
+
+@pytest.mark.parametrize("B,L,d", [
+    # the row-word GEMM2's token tiles of 16, 32, 64 and 128, with 128 and 256 columns
+    (5, 3000, 520), (16, 900, 4104), (32, 3000, 520), (17, 3000, 2056), (64, 3000, 520),
+    (33, 3000, 2568), (127, 3000, 520), (65, 3000, 2312)])
+@pytest.mark.parametrize("dt", [BF16, F16])
+def test_fast_h_tiles(B, L, d, dt):
+    say(f"FAST_H tiles B={B} L={L} d={d} {dt}")
+    p = problem(B, L, d, dt)
+    got = call(*p[:5], flags=si.FLAG_FAST_H)
+    assert not got[3].any()
+    err = rel(got, p[5])
+    say(f"  {err:.2e}")
+    assert err <= ONE_H[dt]
+    assert torch.equal(got, call(*p[:5], flags=si.FLAG_FAST_H))
