@@ -89,7 +89,15 @@ Plan make_plan(int64_t B, int64_t L, int64_t d, int num_cu) {
     p.off_hlo = o;
     o = align256(o + (size_t)B * p.Up * 2);
     p.off_part = o;
-    o = align256(o + (size_t)(p.KS - 1) * B * part_chunks(d) * kChunk * 4);
+    // Where that many chunks' partials alone would take the call past si_selective_ffn_noalloc's
+    // scratch, as few less as fit, down to half (127 tokens x 71117 slots, d = 4264: 67.7 MB with
+    // 15 chunks; a batch of 65 to 127 tokens once had two token tiles and half the chunks, and is
+    // taken as it was then)
+    const size_t row = (size_t)B * part_chunks(d) * kChunk * 4;  // partials of a chunk
+    const size_t room = o < SI_NOALLOC_SCRATCH_BYTES ? SI_NOALLOC_SCRATCH_BYTES - o : 0;
+    const int64_t fit = (int64_t)(room / row) + 1;  // (chunk 0 has none)
+    if (o <= SI_NOALLOC_SCRATCH_BYTES && fit < p.KS && fit >= (p.KS + 1) / 2) p.KS = (int)fit;
+    o = align256(o + (size_t)(p.KS - 1) * row);
     p.total = o;
     return p;
 }
