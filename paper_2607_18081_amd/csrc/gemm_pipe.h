@@ -83,7 +83,8 @@ constexpr int kScanWords = 1024;
 // token. Those are 2 gate and 2 up rows of the same two slots, so SiLU * up needs no data
 // exchange. NX LDS stages of x and NWT of the weight rows, which come from HBM and are given
 // the longer flight where the LDS cannot hold a third stage of both (256 x 256).
-template <typename ET, int MODE, int BM, int BN, int WT, int WW, int NX, int NWT>
+// ONCE: each weight row is read by one work-group.
+template <typename ET, int MODE, int BM, int BN, int WT, int WW, int NX, int NWT, bool ONCE = false>
 __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     const uint16_t* __restrict__ x, int64_t B, int64_t d, const uint16_t* __restrict__ gu, int64_t L,
     int32_t* __restrict__ ulist, int* __restrict__ ucount, const uint32_t* __restrict__ part,
@@ -102,8 +103,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
     static_assert(NX * (LX + LW + (kPart ? 1 : 0)) <= 63, "the load counter has 6 bits");
     static_assert(NWT == NX || (NX == 2 && NWT == 3 && kPart == 0), "stages");
     typedef typename Mfma<ET>::vec8 vec8;
-    // a batch below 128 tokens reads each weight row once
-    constexpr int kWPol = MODE == kWord ? kNonTemporal : 0;
+    constexpr int kWPol = ONCE ? kNonTemporal : 0;
     // one array per stage: the compiler then sees that a stage's reads do not touch the stages
     // being loaded, and waits for nothing between them
     __shared__ __align__(1024) char x0[RX * 1024];
@@ -581,7 +581,9 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
 // value, 2: hi + lo). Chunk 0 goes to y, chunk p > 0 to row p - 1 of the partials.
 // LIST: the union list and its length; otherwise K = slot over W bitmap words, with the token
 // tile's union words (words[tm * W]): a row that no token of the tile has is not loaded.
-template <typename ET, bool LIST, int PL, int BM, int BN, int WT, int WW, int NH, int ND>
+// ONCE: each down row is read by one token tile.
+template <typename ET, bool LIST, int PL, int BM, int BN, int WT, int WW, int NH, int ND,
+          bool ONCE = false>
 __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     const uint16_t* __restrict__ Hhi, const uint16_t* __restrict__ Hlo, int64_t Up, int64_t B,
     const uint16_t* __restrict__ dc, int64_t d, int64_t L, const int32_t* __restrict__ ulist,
@@ -706,7 +708,8 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     };
     auto load_d = [&](char* s) {  // at row_offsets()
 #pragma unroll
-        for (int j = 0; j < LD; ++j) load_lds16<LIST ? 0 : kNonTemporal>(rd, s + (j * NW + w) * 1024, doff[j], 0);
+        for (int j = 0; j < LD; ++j)
+            load_lds16<ONCE ? kNonTemporal : 0>(rd, s + (j * NW + w) * 1024, doff[j], 0);
     };
 
     f32x4_t acc[FW][FT];

@@ -22,7 +22,9 @@
 //    order (chunk 0 goes to y itself).
 // For so few tokens both GEMMs stream the union's rows: they are bound by how much of HBM's
 // latency the loads in flight cover, so the tiles are small and the stages many (70 to 160 KB
-// of LDS a CU), and the row loads carry the non-temporal policy (each row is read once).
+// of LDS a CU), and the row loads carry the non-temporal policy while one token tile reads each
+// row (128 tokens x 524288 slots, d = 512 556 us, default policy 575; with several tiles the
+// others then find fewer rows in L2: 300 tokens x 523900, d = 680 2267 / 2156 us).
 #include <hip/hip_ext.h>
 
 #include "common.h"
@@ -196,43 +198,56 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
     if (e != hipSuccess) return e;
     const dim3 g2((unsigned)((int64_t)p.ntm * p.ntn * p.KS + 7) / 8 * 8);
     const dim3 g1((unsigned)(p.ntm * ((p.W * 32 + p.bn1 / 2 - 1) / (p.bn1 / 2)) + 7) / 8 * 8);
-#define SI_G1(BM, BN, WT, WW, NX)                                                                \
-    hipExtLaunchKernelGGL((gemm1_pipe<ET, kWord, BM, BN, WT, WW, NX, NX>), g1,                   \
+    // (token tiles below 128 hold the whole batch)
+    const bool once = p.ntm == 1;
+#define SI_G1(BM, BN, WT, WW, NX, ONCE)                                                          \
+    hipExtLaunchKernelGGL((gemm1_pipe<ET, kWord, BM, BN, WT, WW, NX, NX, ONCE>), g1,             \
                           dim3(64 * WT * WW), 0, s, ev0, nullptr, 0, xx, B, d, gu, L, nullptr,   \
                           nullptr, nullptr, 0, bits, p.W, hhi, hlo, p.Up, p.ntm, nullptr, words)
-#define SI_G2_PL(PL, BM, BN, WT, WW, NH, ND)                                                     \
-    hipExtLaunchKernelGGL((gemm2_pipe<ET, false, PL, BM, BN, WT, WW, NH, ND>), g2,               \
+#define SI_G1_TILES(BM, BN, WT, WW, NX)                                                          \
+    if (once) SI_G1(BM, BN, WT, WW, NX, true); else SI_G1(BM, BN, WT, WW, NX, false)
+#define SI_G2_PL(PL, BM, BN, WT, WW, NH, ND, ONCE)                                               \
+    hipExtLaunchKernelGGL((gemm2_pipe<ET, false, PL, BM, BN, WT, WW, NH, ND, ONCE>), g2,         \
                           dim3(64 * WT * WW), 0, s, nullptr, ev1, 0, hhi, hlo, p.Up, B, dc, d, L, \
                           nullptr, nullptr, words, p.W, y, part, p.KS, p.ntm, p.ntn)
-#define SI_G2(BM, BN, WT, WW, NH, ND)                                                            \
-    if (fast) SI_G2_PL(1, BM, BN, WT, WW, NH, ND); else SI_G2_PL(2, BM, BN, WT, WW, NH, ND)
+#define SI_G2(BM, BN, WT, WW, NH, ND, ONCE)                                                      \
+    if (fast) SI_G2_PL(1, BM, BN, WT, WW, NH, ND, ONCE);                                         \
+    else SI_G2_PL(2, BM, BN, WT, WW, NH, ND, ONCE)
+#define SI_G2_TILES(BM, BN, WT, WW, NH, ND)                                                      \
+    if (once) {                                                                                  \
+        SI_G2(BM, BN, WT, WW, NH, ND, true);                                                     \
+    } else {                                                                                     \
+        SI_G2(BM, BN, WT, WW, NH, ND, false);                                                    \
+    }
     switch (p.bm * 1000 + p.bn1) {
-        case 16064: SI_G1(16, 64, 1, 2, 8); break;
-        case 16080: SI_G1(16, 80, 1, 1, 5); break;
-        case 16096: SI_G1(16, 96, 1, 2, 8); break;
-        case 16128: SI_G1(16, 128, 1, 2, 7); break;
-        case 32064: SI_G1(32, 64, 2, 2, 8); break;
-        case 32080: SI_G1(32, 80, 2, 1, 8); break;
-        case 32096: SI_G1(32, 96, 2, 2, 8); break;
-        case 32128: SI_G1(32, 128, 2, 2, 7); break;
-        case 64064: SI_G1(64, 64, 2, 2, 8); break;
-        case 64080: SI_G1(64, 80, 4, 1, 8); break;
-        case 64096: SI_G1(64, 96, 2, 2, 7); break;
-        case 64128: SI_G1(64, 128, 2, 2, 6); break;
-        case 128064: SI_G1(128, 64, 2, 2, 6); break;
-        case 128080: SI_G1(128, 80, 4, 1, 6); break;
-        case 128096: SI_G1(128, 96, 2, 2, 5); break;
-        default: SI_G1(128, 128, 2, 2, 4); break;
+        case 16064: SI_G1(16, 64, 1, 2, 8, true); break;
+        case 16080: SI_G1(16, 80, 1, 1, 5, true); break;
+        case 16096: SI_G1(16, 96, 1, 2, 8, true); break;
+        case 16128: SI_G1(16, 128, 1, 2, 7, true); break;
+        case 32064: SI_G1(32, 64, 2, 2, 8, true); break;
+        case 32080: SI_G1(32, 80, 2, 1, 8, true); break;
+        case 32096: SI_G1(32, 96, 2, 2, 8, true); break;
+        case 32128: SI_G1(32, 128, 2, 2, 7, true); break;
+        case 64064: SI_G1(64, 64, 2, 2, 8, true); break;
+        case 64080: SI_G1(64, 80, 4, 1, 8, true); break;
+        case 64096: SI_G1(64, 96, 2, 2, 7, true); break;
+        case 64128: SI_G1(64, 128, 2, 2, 6, true); break;
+        case 128064: SI_G1_TILES(128, 64, 2, 2, 6); break;
+        case 128080: SI_G1_TILES(128, 80, 4, 1, 6); break;
+        case 128096: SI_G1_TILES(128, 96, 2, 2, 5); break;
+        default: SI_G1_TILES(128, 128, 2, 2, 4); break;
     }
     switch (p.bm * 1000 + p.bn2) {
-        case 16128: SI_G2(16, 128, 1, 4, 8, 8); break;
-        case 32128: SI_G2(32, 128, 1, 4, 6, 6); break;
-        case 32256: SI_G2(32, 256, 1, 4, 4, 4); break;
-        case 64128: SI_G2(64, 128, 2, 2, 5, 5); break;
-        case 64256: SI_G2(64, 256, 2, 4, 3, 3); break;
-        case 128128: SI_G2(128, 128, 4, 2, 3, 3); break;
-        default: SI_G2(128, 256, 2, 4, 2, 3); break;
+        case 16128: SI_G2(16, 128, 1, 4, 8, 8, true); break;
+        case 32128: SI_G2(32, 128, 1, 4, 6, 6, true); break;
+        case 32256: SI_G2(32, 256, 1, 4, 4, 4, true); break;
+        case 64128: SI_G2(64, 128, 2, 2, 5, 5, true); break;
+        case 64256: SI_G2(64, 256, 2, 4, 3, 3, true); break;
+        case 128128: SI_G2_TILES(128, 128, 4, 2, 3, 3); break;
+        default: SI_G2_TILES(128, 256, 2, 4, 2, 3); break;
     }
+#undef SI_G1_TILES
+#undef SI_G2_TILES
 #undef SI_G1
 #undef SI_G2
 #undef SI_G2_PL

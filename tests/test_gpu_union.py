@@ -104,3 +104,18 @@ def test_fast_h_tiles(B, L, d, dt):
     say(f"  {err:.2e}")
     assert err <= ONE_H[dt]
     assert torch.equal(got, call(*p[:5], flags=si.FLAG_FAST_H))
+
+
+@pytest.mark.parametrize("B,L,d", [(128, 523800, 64), (130, 524288, 72), (260, 524000, 136)])
+@pytest.mark.parametrize("flags", [0, si.FLAG_FAST_H])
+def test_row_word_tiles_of_large_batches(B, L, d, flags):
+    """More slots than the tiled path takes: the row-word GEMMs at one, two and three tiles of
+    128 tokens."""
+    say(f"row-word B={B} L={L} d={d} flags {flags}")
+    p = problem(B, L, d, density=0.002)
+    got = call(*p[:5], flags=flags)
+    assert not got[3].any()
+    err = rel(got, p[5])
+    say(f"  {err:.2e}")
+    assert err <= (ONE_H[BF16] if flags else 1e-4)
+    assert torch.equal(got, call(*p[:5], flags=flags))
