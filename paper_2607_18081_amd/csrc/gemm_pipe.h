@@ -758,7 +758,9 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
         for (int q = 0; q < PL; ++q)
 #pragma unroll
             for (int j = 0; j < FT; ++j)
-                fh[h][q][j] = Mfma<ET>::vec(ld16(sh + q * BM * 128 + to + j * 2048 + c));
+                // (one sum of offsets: the compiler follows few pointer steps from a stage's
+                // array to its reads, and has a read that it loses wait for every load)
+                fh[h][q][j] = Mfma<ET>::vec(ld16(sh + (q * BM * 128 + to + j * 2048 + c)));
     };
     auto mults = [&](int h) {
 #pragma unroll

@@ -2,7 +2,8 @@
 
 h travels as a hi + lo pair of 16-bit values below 128 tokens and with SI_FLAG_EXACT_H, held to
 1e-4 as elsewhere; as one 16-bit value with SI_FLAG_FAST_H and by default from 128 tokens, where
-rounding it leaves 2^-9 (bf16) or 2^-12 (half) of each product at most."""
+rounding it to 8 (bf16) or 11 (half) significant bits leaves 2^-8 or 2^-11 of each product at
+most."""
 import pytest
 import torch
 
@@ -12,7 +13,7 @@ from tests.gpu_util import say
 pytestmark = pytest.mark.gpu
 
 BF16, F16 = torch.bfloat16, torch.float16
-ONE_H = {BF16: 2.0 ** -9, F16: 2.0 ** -12}
+ONE_H = {BF16: 2.0 ** -8, F16: 2.0 ** -11}
 
 
 def problem(B, L, d, dt=BF16, density=0.2, seed=0, pool=None):
