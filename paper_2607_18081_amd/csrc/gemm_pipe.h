@@ -225,6 +225,22 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm1_pipe(
         if (t >= first && t < 2 && wd + t < W && 32 * t < wsh + kS)
             words[(int64_t)tm * W + wd + t] = (uint32_t)(uword >> (32 * t));
     }
+    // no token has a slot of the tile: h = 0, and nothing else is read (5 tokens with 10 slots
+    // each of 100000, d = 1024: GEMM1 43 us without this)
+    if constexpr (MODE == kWord) {
+        const uint64_t mine = kS == 64 ? uword : (uword >> wsh) & ((1ull << kS) - 1ull);
+        if (mine == 0u) {  // uniform: every wave has the OR over all the tile's tokens
+            const V16 zero = {{0u, 0u, 0u, 0u}};
+            for (int e = t; e < BM * (kS / 8); e += kThr) {
+                const int64_t tok = m0 + e / (kS / 8), u = u0 + 8 * (e % (kS / 8));
+                if (tok < B && u < Up) {
+                    st16(Hhi + tok * Up + u, zero);
+                    if (Hlo) st16(Hlo + tok * Up + u, zero);
+                }
+            }
+            return;
+        }
+    }
     // kUnion: the tile's slots, -1 past the union, in a table for the row offsets; thread t
     // keeps slot t for the epilogue
     int32_t* const stab = reinterpret_cast<int32_t*>(w1);
@@ -669,18 +685,17 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     const int dcol =
         16 * ((lane % (64 / kRpp)) ^ ((((drow & 3) | ((drow >> 3) << 2)) & kF) << 1));
     const int dlim = (int)((d - n0) * 2);  // bytes of a row from the tile's first column on
-    // The slots (or union words) of a step's down rows are read a step ahead of the rows' loads
-    // (a position out of the descriptor's range reads as 0, not used).
+    // LIST: the slots of a step's down rows are read a step ahead of the rows' loads (a position
+    // out of the descriptor's range reads as 0, not used).
     auto load_ids = [&](int k, int32_t(&ids)[LD]) {
 #pragma unroll
-        for (int j = 0; j < LD; ++j) {
-            const int pos = kb + k * kBK + drow + j * kDR;
+        for (int j = 0; j < LD; ++j)
             ids[j] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                ru, LIST ? pos * 4 : (pos >> 5) * 4, 0, 0);
-        }
+                ru, (kb + k * kBK + drow + j * kDR) * 4, 0, 0);
     };
     int32_t nid[LD];  // of the step whose rows are loaded next
-    int doff[LD];
+    int doff[LD];     // the rows' offsets, from dso on
+    int dso = 0;
     auto row_offsets = [&](int k, const int32_t(&ids)[LD]) {
 #pragma unroll
         for (int j = 0; j < LD; ++j) {
@@ -688,28 +703,67 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
             const int col = dcol ^ swz(j);
             // (no short circuits: each would be a branch; d % 8 == 0)
             bool ok = (pos < ke) & (col < dlim);
-            if constexpr (LIST)
-                ok &= (unsigned)ids[j] < (unsigned)L;
-            else
-                ok &= ((uint32_t)ids[j] >> (pos & 31)) & 1u;
-            const int o = (LIST ? ids[j] : pos) * (int)(d * 2) + (int)(n0 * 2) + col;
+            ok &= (unsigned)ids[j] < (unsigned)L;
+            const int o = ids[j] * (int)(d * 2) + (int)(n0 * 2) + col;
             doff[j] = ok ? o : kOOB;
+        }
+    };
+    // Otherwise: the union words of kSeg steps lie in registers, those of step seg + l in lane l,
+    // and um has the non-empty ones among them. The pipeline runs over those only, and anew for
+    // the next kSeg (chunks are seldom that long: 4096 slots).
+    constexpr int kSeg = 64;
+    uint32_t uw0 = 0u, uw1 = 0u;
+    uint64_t um = 0u;
+    int seg = 0;
+    const __amdgpu_buffer_rsrc_t rw = make_rsrc(words + (LIST ? 0 : tm * W), LIST ? 0 : W * 4);
+    auto load_words = [&](int nk) -> int {  // the number of non-empty steps
+        const int o = seg + lane < nk ? ((kb >> 5) + 2 * (seg + lane)) * 4 : kOOB;
+        uw0 = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, o, 0, 0);
+        uw1 = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rw, o + 4, 0, 0);
+        um = __ballot((uw0 | uw1) != 0u);
+        return __popcll(um);
+    };
+    auto next_step = [&]() -> int {  // in the segment; -1: none is left
+        const int p = um ? __builtin_ctzll(um) : -1;
+        um &= um - 1u;
+        return p;
+    };
+    int roff[LD];  // offsets of a step's rows from its first
+    if constexpr (!LIST) {
+#pragma unroll
+        for (int j = 0; j < LD; ++j) {
+            const int col = dcol ^ swz(j);
+            roff[j] = col < dlim ? (drow + j * kDR) * (int)(d * 2) + (int)(n0 * 2) + col : kOOB;
+        }
+    }
+    auto word_offsets = [&](int p) {
+        const uint32_t lo = p < 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)uw0, p & 63);
+        const uint32_t hi = p < 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)uw1, p & 63);
+        dso = p < 0 ? 0 : (kb + (seg + p) * kBK) * (int)(d * 2);
+#pragma unroll
+        for (int j = 0; j < LD; ++j) {
+            const int row = drow + j * kDR;
+            doff[j] = ((row & 32 ? hi : lo) >> (row & 31)) & 1u ? roff[j] : kOOB;
         }
     };
     // loads of step k into stage s (H past the chunk reads as zeros, so that what its rows hold
     // there does not matter)
+    // (k < 0: no step)
     auto load_h = [&](int k, char* s) {
-        const bool ok = 8 * hc < ke - kb - k * kBK;
+        const bool ok = LIST ? 8 * hc < ke - kb - k * kBK
+                             : (k >= 0) & (8 * hc < ke - kb - (seg + k) * kBK);
+        const int so = LIST ? k * 128 : k < 0 ? 0 : (seg + k) * 128;
 #pragma unroll
         for (int j = 0; j < LH; ++j)
             load_lds16(HP >= NW && j * NW >= HP ? rl : rh, s + (j * NW + w) * 1024,
                        ok ? hoff + (HP >= NW ? j % (HP / (HP < NW ? HP : NW)) : 0) * hstep : kOOB,
-                       k * 128);
+                       so);
     };
-    auto load_d = [&](char* s) {  // at row_offsets()
+    auto load_d = [&](char* s) {  // at row_offsets() or word_offsets()
 #pragma unroll
         for (int j = 0; j < LD; ++j)
-            load_lds16<ONCE ? kNonTemporal : 0>(rd, s + (j * NW + w) * 1024, doff[j], 0);
+            load_lds16<ONCE ? kNonTemporal : 0>(rd, s + (j * NW + w) * 1024, doff[j],
+                                               LIST ? 0 : dso);
     };
 
     f32x4_t acc[FW][FT];
@@ -775,6 +829,7 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     char* const ds[8] = {d0, d1, d2, d3, d4, d5, d6, d7};
     // A K step, as in GEMM1. The offsets of the next down loads are formed from their slots just
     // before the barrier; the slots after those are then asked for, a step ahead of their use.
+    int hnext = -1;  // with kSplit: the step whose H loads follow (its down loads go first)
     constexpr int NM = PL * FT * FW, NR = PL * FT + 2 * FW;
     constexpr int LA = kSplit ? LD : 0, LB = LH + (kSplit ? 0 : LD);
     auto step = [&](int k, int q) {
@@ -791,12 +846,23 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
         __builtin_amdgcn_sched_barrier(0);
         // the next step's loads have landed: at least these many were issued after them
         wait_vm_lds<kSplit ? LD : (NH - 2) * (LH + LD)>();
-        row_offsets(k + ND, nid);
+        int pn = -1;
+        if constexpr (LIST) {
+            row_offsets(k + ND, nid);
+        } else {
+            pn = next_step();
+            word_offsets(pn);
+        }
         wg_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        load_ids(k + ND + 1, nid);
-        __builtin_amdgcn_sched_barrier(0);
-        load_h(k + NH, hs[q % NH]);
+        if constexpr (LIST) {
+            load_ids(k + ND + 1, nid);
+            __builtin_amdgcn_sched_barrier(0);
+            load_h(k + NH, hs[q % NH]);
+        } else {
+            load_h(kSplit ? hnext : pn, hs[q % NH]);
+            hnext = pn;
+        }
         if constexpr (!kSplit) load_d(ds[q % ND]);
         frags(hs[(q + 1) % NH], ds[(q + 1) % ND], 0);
         mults(1);
@@ -821,32 +887,54 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     };
     if (kb < ke) {
         const int nk = (ke - kb + kBK - 1) / kBK;
-        int32_t pid[ND][LD];
+        int n = nk;  // steps to run
+        do {
+            if constexpr (LIST) {
+                int32_t pid[ND][LD];
 #pragma unroll
-        for (int q = 0; q < ND; ++q) load_ids(q, pid[q]);
-        load_ids(ND, nid);
-        __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < ND; ++q) load_ids(q, pid[q]);
+                load_ids(ND, nid);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < NH; ++q) {
-            row_offsets(q, pid[q]);
-            load_h(q, hs[q]);
-            load_d(ds[q]);
-            __builtin_amdgcn_sched_barrier(0);  // the counted waits rely on the stages' order
-        }
-        if constexpr (kSplit) row_offsets(ND - 1, pid[ND - 1]);  // step 0 loads these rows
-        wait_vm_lds<(NH - 1) * (LH + LD)>();
-        wg_barrier();
-        frags(h0, d0, 0);
-        int k = 0;
-        for (; k + kPer <= nk; k += kPer) {
+                for (int q = 0; q < NH; ++q) {
+                    row_offsets(q, pid[q]);
+                    load_h(q, hs[q]);
+                    load_d(ds[q]);
+                    __builtin_amdgcn_sched_barrier(0);  // the counted waits rely on this order
+                }
+                if constexpr (kSplit) row_offsets(ND - 1, pid[ND - 1]);  // for step 0
+            } else {
+                n = load_words(nk);
+                if (n == 0) continue;  // uniform: every wave reads the same words
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) step(k + q, q);
-        }
+                for (int q = 0; q < NH; ++q) {
+                    const int p = next_step();
+                    word_offsets(p);
+                    load_h(p, hs[q]);
+                    load_d(ds[q]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (kSplit) {
+                    hnext = next_step();
+                    word_offsets(hnext);
+                }
+            }
+            wait_vm_lds<(NH - 1) * (LH + LD)>();
+            wg_barrier();
+            frags(h0, d0, 0);
+            int k = 0;
+            for (; k + kPer <= n; k += kPer) {
 #pragma unroll
-        for (int q = 0; q < kPer - 1; ++q)
-            if (k + q < nk) step(k + q, q);
+                for (int q = 0; q < kPer; ++q) step(k + q, q);
+            }
+#pragma unroll
+            for (int q = 0; q < kPer - 1; ++q)
+                if (k + q < n) step(k + q, q);
+            wait_vm_lds<0>();  // nothing may land in LDS once the work-group is gone
+            if constexpr (!LIST) wg_barrier();  // every wave has read the segment's last stages
+        } while (!LIST && (seg += kSeg) < nk);
         if constexpr (kRuns) flush_sums(tot, acc);
-        wait_vm_lds<0>();  // nothing may land in LDS once the work-group is gone
     }
 
     // element e of acc[i][j]: column n0 + 16 (ww FW + i) + 4 g + e of token

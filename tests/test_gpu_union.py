@@ -3,7 +3,7 @@
 h travels as a hi + lo pair of 16-bit values below 128 tokens and with SI_FLAG_EXACT_H, held to
 1e-4 as elsewhere; as one 16-bit value with SI_FLAG_FAST_H and by default from 128 tokens, where
 rounding it to 8 (bf16) or 11 (half) significant bits leaves 2^-8 or 2^-11 of each product at
-most."""
+most, and of the sum where one product outweighs the others."""
 import pytest
 import torch
 
@@ -120,3 +120,63 @@ def test_row_word_tiles_of_large_batches(B, L, d, flags):
     say(f"  {err:.2e}")
     assert err <= (ONE_H[BF16] if flags else 1e-4)
     assert torch.equal(got, call(*p[:5], flags=flags))
+
+
+def sparse_pool(L, how):
+    g = torch.Generator(device="cuda").manual_seed(L)
+    if how == "none":
+        return torch.zeros(0, dtype=torch.int64, device="cuda")
+    if how == "ends":
+        return torch.tensor([0, L - 1], device="cuda")
+    if how == "run":
+        return torch.arange(L // 3, L // 3 + 100, device="cuda")
+    return torch.randperm(L, device="cuda", generator=g)[:60].sort().values
+
+
+@pytest.mark.parametrize("B,L,d", [
+    # token tiles of 16 to 128 and both column tiles; the last two have K chunks of several times
+    # the 64 steps whose union words are held at a time
+    (5, 7706, 520), (16, 30000, 2056), (32, 9000, 1032), (33, 9000, 2568), (64, 16000, 136),
+    (100, 20000, 264), (127, 12000, 2312), (300, 524000, 520), (5, 48000, 11000)])
+@pytest.mark.parametrize("how", ["none", "ends", "run", "spread"])
+def test_sparse_unions(B, L, d, how):
+    """Unions of few slots: tiles and K steps without any are passed over."""
+    say(f"sparse union B={B} L={L} d={d} {how}")
+    p = problem(B, L, d, density=0.5, pool=sparse_pool(L, how))
+    for flags in (0, si.FLAG_FAST_H):
+        got = call(*p[:5], flags=flags)
+        if how == "none":
+            assert not got.any()
+            continue
+        assert not got[3].any()
+        err = rel(got, p[5])
+        say(f"  flags {flags}: {err:.2e}")
+        assert err <= (ONE_H[BF16] if flags else 1e-4)
+        assert torch.equal(got, call(*p[:5], flags=flags))
+
+
+def test_sparse_union_costs_its_rows():
+    """Time follows the union's rows, not the loaded slots: 5 tokens without any active slot take
+    under a third of the time of the same call with a fifth of the slots active (measured: a
+    sixth; more than a half while every tile and step was run)."""
+    B, L, d = 5, 131000, 1024
+    full = problem(B, L, d)
+    none = problem(B, L, d, pool=sparse_pool(L, "none"))
+    time = []
+    for p in (full, none):
+        ws = torch.empty(si.selective_ffn_workspace(B, p[2].numel(), L, d), dtype=torch.uint8,
+                         device="cuda")
+        y = torch.empty((B, d), dtype=torch.float32, device="cuda")
+        best = float("inf")
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(20):
+                si.selective_ffn(*p[:5], y=y, workspace=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 20)
+        time.append(best)
+    say(f"full {time[0] * 1e3:.1f} us, none {time[1] * 1e3:.1f} us")
+    assert time[1] <= time[0] / 3
