@@ -38,9 +38,12 @@ def sources() -> list[str]:
     return sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hip"))
 
 
-# the compiler's per-kernel resource remarks: kernel name, then (among others) its VGPR count
-# and its scratch bytes per lane (register spills)
-_REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]): (\S+)")
+# the compiler's per-kernel resource remarks: kernel name, then (among others) its VGPR count,
+# its scratch bytes per lane (register spills) and the waves a SIMD can hold by its registers
+_REMARK = re.compile(r"remark:\s+(Function Name|VGPRs|ScratchSize \[bytes/lane\]|"
+                     r"Occupancy \[waves/SIMD\]): (\S+)")
+_FIELD = {"VGPRs": "vgprs", "ScratchSize [bytes/lane]": "scratch_bytes_per_lane",
+          "Occupancy [waves/SIMD]": "waves_per_simd"}
 
 
 def _compile(src: str) -> tuple[str, list]:
@@ -55,7 +58,7 @@ def _compile(src: str) -> tuple[str, list]:
             cur = {"kernel": val, "source": os.path.basename(src)}
             usage.append(cur)
         elif cur is not None:
-            cur["vgprs" if key == "VGPRs" else "scratch_bytes_per_lane"] = int(val)
+            cur[_FIELD[key]] = int(val)
     return obj, usage
 
 

@@ -3,21 +3,19 @@
 //
 // Order: key = |s| (ABS) or s (RAW); larger key first; equal keys -> lower index first;
 // -0 == +0; NaN after every number. Each float key is mapped to a uint32 whose unsigned order
-// is that order (NaN -> 0); counts are taken as unsigned integers directly. One 1024-thread
-// work-group per row:
-//   1. radix select over 8-bit digits from the top: a histogram of the candidates that match
-//      the prefix found so far gives the next digit of the k-th largest key T and how many
-//      keys equal to T must still be taken (take_eq);
+// is that order (NaN -> 0); counts are taken as unsigned integers directly. One work-group per
+// row:
+//   1. radix select from the top: a histogram of the candidates by their next digit gives the
+//      digit of the k-th largest key T and how many keys equal to T must still be taken;
 //   2. selection in index order: an element is selected iff key > T, or key == T and fewer
-//      than take_eq equal keys precede it; block-wide prefix counts give each selected element
+//      than that many equal keys precede it; block-wide prefix counts give each selected element
 //      its output position, so the output is ascending without a sort.
 // Rows of up to 32768 keys (topk_rows_reg): thread t holds the C contiguous keys t*C .. in
-// registers, read once; each wave counts into its own LDS histogram (16 x 256 bins), the bins
-// are added in wave order and every wave searches them with a DPP scan (two barriers a pass).
-// The digits start below the bits all candidates share, the search stops once the whole
-// bucket of T's prefix is taken (the lower bits cannot change the choice), and then the
-// selection needs no scan of equal keys. The choice can also be written as a bitmap per row,
-// or joined with a given set. Longer rows (topk_rows) re-read the row in each of 4 passes.
+// registers, read once. The digits cover the range between the least and the largest candidate,
+// the search stops once the whole bin of T is taken (the lower bits cannot change the choice;
+// the selection then needs no scan of equal keys), and a bin of at most 64 candidates is ranked
+// by one wave. The choice can also be written as a bitmap per row, or joined with a given set.
+// Longer rows (topk_rows) are read again in each of 4 passes of 8 bits.
 #include "common.h"
 #include "launch.h"
 
@@ -135,7 +133,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows(const float* __restric
     }
 }
 
-// Exclusive prefix sum of v over the block in thread order; *total = block sum. Two barriers.
+// Exclusive prefix sum of v over the block (NW waves) in thread order; *total = block sum. Two
+// barriers.
+template <int NW>
 __device__ __forceinline__ int block_excl_scan(int v, int* wave_tot, int* total) {
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
@@ -144,7 +144,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* wave_tot, int* total)
     __syncthreads();
     int before = 0, all = 0;
 #pragma unroll
-    for (int q = 0; q < kTopkWaves; ++q) {
+    for (int q = 0; q < NW; ++q) {
         const int c = wave_tot[q];
         before += q < w ? c : 0;
         all += c;
@@ -169,34 +169,38 @@ struct TopkOut {
     int* ucount;
 };
 
-constexpr int kDigit = 11, kBins = 1 << kDigit;  // bits and bins of a pass
-constexpr int kOwn = kBins / kTopkThreads;       // bins a thread adds up
-constexpr int kHists = 4;                        // copies of the histogram, for the waves in turn
 constexpr int kMaxRegKeys = 32 * kTopkThreads;  // the register-resident kernel's longest row
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int C>
-__global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __restrict__ scores,
-                                                             int64_t L, int64_t ld, int64_t k,
-                                                             int mode, TopkOut o) {
+// NT threads a row, at least WPS waves a SIMD: two 1024-thread work-groups share a CU with 8
+// only, and the compiler must be told (left alone it takes 106 scalar registers for C = 8: 7
+// waves). digit: bits of a pass, at most kDigit.
+constexpr int kDigit = 11;
+template <int C, int NT, int WPS>
+__global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict__ scores,
+                                                         int64_t L, int64_t ld, int64_t k,
+                                                         int mode, int digit, TopkOut o) {
     static_assert(32 % C == 0, "a thread's keys lie in one bitmap word");
+    constexpr int NW = NT / kWave;
+    constexpr int kBins = 1 << kDigit;
+    constexpr int kOwn = kBins / NT;  // bins a thread adds up, at most
     const int64_t b = blockIdx.x;
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int w = t >> 6;
-    __shared__ int hist[kHists][kBins + 1];  // copies a bank apart
-    __shared__ int wave_tot[kTopkWaves];
-    __shared__ uint32_t s_min[kTopkWaves], s_max[kTopkWaves];
+    __shared__ int hist[kBins];
+    __shared__ int wave_tot[NW];
+    __shared__ uint32_t s_min[NW], s_max[NW];
     __shared__ int s_digit, s_take, s_n;
     __shared__ uint32_t s_key;
     __shared__ uint32_t few[kWave];
     __shared__ int n_few;
     __shared__ uint32_t jbits[kMaxRegKeys / 32];
     if (o.ulist) {  // the joined set as a bitmap
-        for (int q = t; q < kMaxRegKeys / 32; q += kTopkThreads) jbits[q] = 0u;
+        for (int q = t; q < kMaxRegKeys / 32; q += NT) jbits[q] = 0u;
         __syncthreads();
-        for (int64_t i = t; i < o.n_join; i += kTopkThreads) {
+        for (int64_t i = t; i < o.n_join; i += NT) {
             const int32_t v = o.join_ids[i];
             if (v >= 0 && v < L) atomicOr(&jbits[v >> 5], 1u << (v & 31));
         }
@@ -241,21 +245,21 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
         s_min[w] = wmin;
         s_max[w] = wmax;
     }
-    for (int q = t; q < kHists * (kBins + 1); q += kTopkThreads) (&hist[0][0])[q] = 0;
+    for (int q = t; q < kBins; q += NT) hist[q] = 0;
     if (t == 0) n_few = 0;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < kTopkWaves; ++q) {
+    for (int q = 0; q < NW; ++q) {
         kmin = s_min[q] < kmin ? s_min[q] : kmin;
         kmax = s_max[q] > kmax ? s_max[q] : kmax;
     }
-    // The k-th largest key T lies in [base, base + span]; a pass splits that into 2^11 bins of
-    // 2^shift keys. (No candidates at all: nothing is counted, and the first pass ends it.)
+    // The k-th largest key T lies in [base, base + span]; a pass splits that into 2^digit
+    // bins of 2^shift keys. (No candidates at all: nothing is counted, and the first pass ends it.)
     const uint32_t range = kmax - kmin;
     const int width = range ? 32 - __clz((int)range) : 0;
-    int shift = width > kDigit ? width - kDigit : 0;
+    int shift = width > digit ? width - digit : 0;
     uint32_t base = kmin, span = ~0u;
-    int* const my_hist = hist[w % kHists];
+    const int bins = 1 << digit, own = bins / NT;  // (NT <= 1024, digit >= 10)
     int take = (int)k;   // how many still to take among the candidates in the range
     bool done = k == 0;  // all of them are taken
     while (!done) {
@@ -267,31 +271,30 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
             if (((cand >> j) & 1u) && key[j] - base <= span) {
                 const int dg = (int)((key[j] - base) >> shift);
                 if (dg != cur) {
-                    if (cnt) atomicAdd(&my_hist[cur], cnt);
+                    if (cnt) atomicAdd(&hist[cur], cnt);
                     cur = dg;
                     cnt = 0;
                 }
                 ++cnt;
             }
         }
-        if (cnt) atomicAdd(&my_hist[cur], cnt);
+        if (cnt) atomicAdd(&hist[cur], cnt);
         __syncthreads();
-        // 2. the copies added (and cleared for the next pass): thread t owns kOwn bins, the
-        //    largest digits in the lowest threads, and a block-wide scan counts the keys above
+        // 2. the bins read (and cleared for the next pass): thread t owns `own` bins, the largest
+        //    digits in the lowest threads, and a block-wide scan counts the keys above
         int c[kOwn], sum = 0;
 #pragma unroll
         for (int e = 0; e < kOwn; ++e) {
-            const int bin = kBins - 1 - kOwn * t - e;
             c[e] = 0;
-#pragma unroll
-            for (int q = 0; q < kHists; ++q) {
-                c[e] += hist[q][bin];
-                hist[q][bin] = 0;
+            if (e < own) {
+                const int bin = bins - 1 - own * t - e;
+                c[e] = hist[bin];
+                hist[bin] = 0;
             }
             sum += c[e];
         }
         int all;
-        int above = block_excl_scan(sum, wave_tot, &all);
+        int above = block_excl_scan<NW>(sum, wave_tot, &all);
         if (all < take) {  // k above the number of candidates: every candidate is taken
             base = 0u;
             done = true;
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
 #pragma unroll
         for (int e = 0; e < kOwn; ++e) {
             if (above < take && above + c[e] >= take) {
-                s_digit = kBins - 1 - kOwn * t - e;
+                s_digit = bins - 1 - own * t - e;
                 s_take = take - above;
                 s_n = c[e];
             }
@@ -314,10 +317,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
         const int n = s_n;  // candidates in the bin
         done = take == n;
         if (done || shift == 0) break;
-        shift = shift > kDigit ? shift - kDigit : 0;
+        shift = shift > digit ? shift - digit : 0;
         if (n > kWave) continue;
         // 4. no more candidates than lanes: they are gathered, one a lane, and one wave ranks
-        //    them by comparing each with all (all 16 waves at it take 1 us longer)
+        //    them by comparing each with all (all waves at it take 1 us longer)
 #pragma unroll
         for (int j = 0; j < C; ++j)
             if (((cand >> j) & 1u) && key[j] - base <= span) few[atomicAdd(&n_few, 1)] = key[j];
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
 #pragma unroll
         for (int j = 0; j < C; ++j) n_eq += (((cand >> j) & 1u) && key[j] == T) ? 1 : 0;
         int eq_all;
-        int eq_before = block_excl_scan(n_eq, wave_tot, &eq_all);
+        int eq_before = block_excl_scan<NW>(n_eq, wave_tot, &eq_all);
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const bool ok = (cand >> j) & 1u;
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
         cap = o.ucap;
     }
     int sel_all;
-    int pos = block_excl_scan(__popc(sel), wave_tot, &sel_all);
+    int pos = block_excl_scan<NW>(__popc(sel), wave_tot, &sel_all);
 #pragma unroll
     for (int j = 0; j < C; ++j) {
         const bool on = (sel >> j) & 1u;
@@ -395,32 +398,44 @@ __global__ __launch_bounds__(kTopkThreads) void topk_rows_reg(const float* __res
 
 namespace {
 
-// One register-resident launch: C keys per thread (L <= 1024 C), one work-group per row.
-template <int C>
-void launch_reg_c(const float* scores, int64_t B, int64_t L, int64_t ld, int64_t k, int mode,
-                  const TopkOut& o, hipStream_t s) {
-    hipLaunchKernelGGL(topk_rows_reg<C>, dim3((unsigned)B), dim3(kTopkThreads), 0, s, scores, L,
-                       ld, k, mode, o);
-}
-
-// false when a row has more than 32768 keys
+// One register-resident launch, one work-group per row; false when a row has more than 32768
+// keys. What a row costs beside its keys goes by the work-group's threads (scans over the waves,
+// barriers, bins), so rows of few keys take 512 of them, and so do rows of up to 4096 keys where a
+// CU has more than one; with fewer rows than CUs a row of more than 2048 is quicker with 1024 (256
+// rows of 3000 keys by |value| 7.2 / 6.3 us with 512 / 1024 threads, of 2047 5.8 / 5.7; 300 rows
+// of 3000 8.0 / 10.5, of 64 3.9 / 5.3). Rows of 4097 to 8192 keys on shared CUs need 8 waves a
+// SIMD (300 rows of 4500 keys 14.8 / 12.6 us, of 7706 17.0 / 14.8), which costs 0.7 us where a CU
+// has one.
+// Passes of 11 bits by |value| and for counts; 10 by value, whose keys span both signs (256 rows
+// of 3000 keys by value 6.5 / 8.3 us with 10 / 11 bits, of 7706 by |value| 10.8 / 9.7).
 bool launch_reg(const float* scores, int64_t B, int64_t L, int64_t ld, int64_t k, int mode,
                 const TopkOut& o, hipStream_t s) {
-    const int64_t per = (L + kTopkThreads - 1) / kTopkThreads;  // keys per thread
-    if (per <= 1)
-        launch_reg_c<1>(scores, B, L, ld, k, mode, o, s);
-    else if (per <= 2)
-        launch_reg_c<2>(scores, B, L, ld, k, mode, o, s);
-    else if (per <= 4)
-        launch_reg_c<4>(scores, B, L, ld, k, mode, o, s);
-    else if (per <= 8)
-        launch_reg_c<8>(scores, B, L, ld, k, mode, o, s);
-    else if (per <= 16)
-        launch_reg_c<16>(scores, B, L, ld, k, mode, o, s);
-    else if (per <= 32)
-        launch_reg_c<32>(scores, B, L, ld, k, mode, o, s);
+    const int digit = mode == 1 ? 10 : kDigit;
+    const bool shared_cu = B > current_cu_count();
+#define SI_TOPK(C, NT, WPS)                                                                      \
+    hipLaunchKernelGGL((topk_rows_reg<C, NT, WPS>), dim3((unsigned)B), dim3(NT), 0, s, scores, L, \
+                       ld, k, mode, digit, o)
+    if (L <= 512)
+        SI_TOPK(1, 512, 1);
+    else if (L <= 1024)
+        SI_TOPK(2, 512, 1);
+    else if (L <= 2048)
+        SI_TOPK(4, 512, 1);
+    else if (L <= 4096 && shared_cu)
+        SI_TOPK(8, 512, 1);
+    else if (L <= 4096)
+        SI_TOPK(4, 1024, 1);
+    else if (L <= 8192 && shared_cu)
+        SI_TOPK(8, 1024, 8);
+    else if (L <= 8192)
+        SI_TOPK(8, 1024, 1);
+    else if (L <= 16384)
+        SI_TOPK(16, 1024, 1);
+    else if (L <= kMaxRegKeys)
+        SI_TOPK(32, 1024, 1);
     else
         return false;
+#undef SI_TOPK
     return true;
 }
 

@@ -66,6 +66,8 @@ hipError_t launch_activations_mfma(const void* x, int64_t T, int64_t d, const vo
 // each), and an upper bound over L for sizing a workspace
 int activation_tiles(int64_t T, int64_t L);
 int activation_tiles_max(int64_t T);
+// compute units of the current device
+int current_cu_count();
 // ascending list of the set bits of bits[0..W) and their number
 hipError_t launch_bits_to_list(const uint32_t* bits, int64_t W, int32_t* list, int* count,
                                hipStream_t s);

@@ -231,3 +231,21 @@ def test_topk_bins(L):
                 nan = np.isnan(x[b])
                 order = np.lexsort((np.arange(L), nan, -key))
                 assert np.array_equal(got[b], np.sort(order[:k])), (k, mode, b)
+
+
+@pytest.mark.parametrize("L", [1, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193])
+@pytest.mark.parametrize("B", [2, 1100])
+def test_topk_rows_per_cu(B, L):
+    """Every form of the register-resident top-k at the edges of its range of row lengths, with
+    fewer rows than CUs and with several a CU, by value and by |value|; whole numbers beside normal
+    ones, so that equal keys cross the boundary."""
+    say(f"topk rows B={B} L={L}")
+    rng = np.random.default_rng(B + L)
+    x = rng.standard_normal((B, L)).astype(np.float32)
+    x[::2] = np.round(4 * x[::2])
+    dx = dev_tensor(x)
+    for k in sorted({1, (L + 2) // 3, L}):
+        for mode in ("raw", "abs"):
+            key = x if mode == "raw" else np.abs(x)
+            want = np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+            assert np.array_equal(host_array(si.select_topk(dx, k, mode)), want), (k, mode)

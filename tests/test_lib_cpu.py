@@ -167,6 +167,25 @@ def test_product_path_fails_without_library(monkeypatch, tmp_path):
         _lib.load()
 
 
+def test_topk_rows_share_a_cu():
+    """The top-k of many rows of up to 8192 keys: two work-groups of every such instance fit a CU's
+    4 SIMDs (with one, the rows of a CU run one after the other). Instances by keys a thread and
+    threads; <4, 1024> and the first <8, 1024> serve fewer rows than CUs."""
+    import json
+    import os
+    import re
+    from paper_2607_18081_amd import build as b
+    if not os.path.exists(b.USAGE):
+        pytest.skip("the library was not built by build() in this tree (no resource record)")
+    seen = {}
+    for u in json.load(open(b.USAGE)):
+        m = re.search(r"topk_rows_regILi(\d+)ELi(\d+)ELi(\d+)E", u["kernel"])
+        if m:
+            seen[tuple(map(int, m.groups()))] = u["waves_per_simd"]
+    for c, threads, wps in ((1, 512, 1), (2, 512, 1), (4, 512, 1), (8, 512, 1), (8, 1024, 8)):
+        assert seen[c, threads, wps] * 4 * 64 >= 2 * threads, (c, threads, wps)
+
+
 def test_no_kernel_spills():
     """Every kernel instance in the library keeps its state in registers: no scratch (register
     spill) memory, by the compiler's per-kernel resource remarks recorded at build time."""
