@@ -144,6 +144,20 @@ size_t si_selective_ffn_workspace(int64_t B, int64_t nnz, int64_t L, int64_t d,
                                   si_dtype xdt, si_dtype wdt, int flags);
 
 /*
+ * The path and tiles that si_selective_ffn takes for these sizes and flags (for tests and
+ * measurements; nothing is launched), as six int32:
+ *   plan[0]     path: 0 per token, 1 union by bitmap words, 2 union by a slot list
+ *   plan[1..2]  GEMM1 tile: tokens, weight rows (two a slot); 0 on the per-token path
+ *   plan[3..4]  GEMM2 tile: tokens, columns; 0 on the per-token path
+ *   plan[5]     K chunks of GEMM2 (per-token path: work-groups a token)
+ * si_activations_plan: tile[0..1], the tokens and weight rows of the MFMA kernel's tile for the
+ * activations and Eq. 1 scores of T tokens (16-bit data).
+ */
+int si_selective_ffn_plan(int64_t B, int64_t nnz, int64_t L, int64_t d, si_dtype xdt,
+                          si_dtype wdt, int flags, int32_t* plan);
+int si_activations_plan(int64_t T, int64_t L, int32_t* tile);
+
+/*
  * Selective computation (Selective Computation section) of one compacted SwiGLU FFN layer
  * for B tokens:
  *

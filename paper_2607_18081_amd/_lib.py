@@ -25,6 +25,8 @@ SIGNATURES = {
     "si_select_topk_workspace": (c_size, [c_i64, c_i64, c_i64]),
     "si_select_topk": (c_int, [c_vp, c_i64, c_i64, c_i64, c_int, c_vp, c_vp, c_size, c_vp]),
     "si_selective_ffn_workspace": (c_size, [c_i64, c_i64, c_i64, c_i64, c_int, c_int, c_int]),
+    "si_selective_ffn_plan": (c_int, [c_i64, c_i64, c_i64, c_i64, c_int, c_int, c_int, c_vp]),
+    "si_activations_plan": (c_int, [c_i64, c_i64, c_vp]),
     "si_selective_ffn": (c_int, [c_vp, c_int, c_i64, c_i64, c_vp, c_vp, c_i64, c_vp, c_vp,
                                  c_i64, c_int, c_vp, c_vp, c_size, c_int, c_vp]),
     "si_selective_ffn_noalloc": (c_int, [c_vp, c_int, c_i64, c_i64, c_vp, c_vp, c_i64, c_vp, c_vp,

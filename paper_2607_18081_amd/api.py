@@ -145,6 +145,23 @@ def selective_ffn_workspace(B: int, nnz: int, L: int, d: int, xdt=BF16, wdt=BF16
     return int(load().si_selective_ffn_workspace(B, nnz, L, d, xdt, wdt, flags))
 
 
+def selective_ffn_plan(B: int, nnz: int, L: int, d: int, xdt=BF16, wdt=BF16,
+                       flags: int = 0) -> tuple:
+    """si_selective_ffn_plan: (path, GEMM1 tile tokens, weight rows, GEMM2 tile tokens, columns,
+    K chunks) of a call of these sizes. Needs no GPU."""
+    out = (ctypes.c_int32 * 6)()
+    _check(load().si_selective_ffn_plan(B, nnz, L, d, xdt, wdt, flags, out),
+           "si_selective_ffn_plan")
+    return tuple(out)
+
+
+def activations_plan(T: int, L: int) -> tuple:
+    """si_activations_plan: (tokens, weight rows) of the MFMA activation kernel's tile."""
+    out = (ctypes.c_int32 * 2)()
+    _check(load().si_activations_plan(T, L, out), "si_activations_plan")
+    return tuple(out)
+
+
 _WS: dict = {}
 
 

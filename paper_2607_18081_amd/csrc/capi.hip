@@ -252,6 +252,26 @@ size_t si_selective_ffn_workspace(int64_t B, int64_t nnz, int64_t L, int64_t d, 
     return si::decode_workspace(B, nnz, d, ncu);
 }
 
+int si_selective_ffn_plan(int64_t B, int64_t nnz, int64_t L, int64_t d, si_dtype xdt,
+                          si_dtype wdt, int flags, int32_t* plan) {
+    if (B < 1 || d < 1 || L < 1 || nnz < 0 || !plan) return SI_ERR_INVALID;
+    if (!valid_pair(xdt, wdt) || si::decode_supported(xdt, wdt, d)) return SI_ERR_UNSUPPORTED;
+    const int dev = current_device();
+    const int ncu = dev < 0 ? 256 : num_cu(dev);
+    for (int i = 0; i < 6; ++i) plan[i] = 0;
+    if (use_union(B, L, d, xdt, wdt, flags))
+        si::union_tiles(B, nnz, L, d, ncu, flags, plan);
+    else
+        plan[5] = si::decode_chunks(B, nnz, ncu);
+    return SI_OK;
+}
+
+int si_activations_plan(int64_t T, int64_t L, int32_t* tile) {
+    if (T < 1 || L < 1 || !tile) return SI_ERR_INVALID;
+    si::activation_tile(T, L, tile);
+    return SI_OK;
+}
+
 int si_selective_ffn(const void* x, si_dtype xdt, int64_t B, int64_t d, const int32_t* offsets,
                      const int32_t* idx, int64_t nnz, const void* gate_up_c, const void* down_c,
                      int64_t L, si_dtype wdt, float* y, void* ws, size_t ws_bytes, int flags,

@@ -175,6 +175,14 @@ size_t union_workspace(int64_t B, int64_t L, int64_t d, int num_cu, int flags) {
     return make_plan(B, L, d, num_cu).total;
 }
 
+void union_tiles(int64_t B, int64_t nnz, int64_t L, int64_t d, int num_cu, int flags,
+                 int32_t* plan) {
+    if (use_tiled(B, L, d)) return tiled_tiles(B, nnz, L, d, num_cu, flags, plan);
+    const Plan p = make_plan(B, L, d, num_cu);
+    const int32_t out[6] = {1, p.bm, p.bn1, p.bm, p.bn2, p.KS};
+    for (int i = 0; i < 6; ++i) plan[i] = out[i];
+}
+
 namespace {
 
 template <typename ET>

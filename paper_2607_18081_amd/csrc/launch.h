@@ -36,6 +36,9 @@ hipError_t launch_decode(const void* x, int xdt, int64_t B, int64_t d, const int
 // sizes the union kernels handle (their buffer loads take 32-bit byte offsets)
 bool union_supported(int64_t B, int64_t L, int64_t d);
 size_t union_workspace(int64_t B, int64_t L, int64_t d, int num_cu, int flags);
+// plan[0..5] of si_selective_ffn_plan
+void union_tiles(int64_t B, int64_t nnz, int64_t L, int64_t d, int num_cu, int flags,
+                 int32_t* plan);
 // et: the 16-bit element type of x and the weights (1 = bf16, 2 = IEEE half)
 hipError_t launch_union(const void* x, int64_t B, int64_t d, const int32_t* offsets,
                         const int32_t* idx, int64_t nnz, const void* gate_up_c,
@@ -50,6 +53,8 @@ hipError_t launch_token_bitmaps(const int32_t* offsets, const int32_t* idx, int6
 // ---- k_tiled.hip: union path for large batches (LDS-tiled MFMA GEMMs) ----------------------
 bool tiled_supported(int64_t B, int64_t L, int64_t d);
 size_t tiled_workspace(int64_t B, int64_t L, int64_t d, int num_cu, int flags);
+void tiled_tiles(int64_t B, int64_t nnz, int64_t L, int64_t d, int num_cu, int flags,
+                 int32_t* plan);
 hipError_t launch_union_tiled(const void* x, int64_t B, int64_t d, const int32_t* offsets,
                               const int32_t* idx, int64_t nnz, const void* gate_up_c,
                               const void* down_c, int64_t L, int et, float* y, void* ws,
@@ -57,7 +62,7 @@ hipError_t launch_union_tiled(const void* x, int64_t B, int64_t d, const int32_t
                               hipEvent_t ev1);
 
 // all-slots modes of the tiled GEMM1 (bf16): activations out[t * ldo + j] (score = 0) or one
-// Eq. 1 partial row per 256-token tile, out[tile * ldo + j] (score = 1)
+// Eq. 1 partial row per token tile, out[tile * ldo + j] (score = 1)
 hipError_t launch_activations_mfma(const void* x, int64_t T, int64_t d, const void* gate_up_c,
                                    int64_t L, int et, float* out, int64_t ldo, int score,
                                    hipStream_t s, hipEvent_t ev0 = nullptr,
@@ -66,6 +71,8 @@ hipError_t launch_activations_mfma(const void* x, int64_t T, int64_t d, const vo
 // each), and an upper bound over L for sizing a workspace
 int activation_tiles(int64_t T, int64_t L);
 int activation_tiles_max(int64_t T);
+// its tile: tokens, weight rows
+void activation_tile(int64_t T, int64_t L, int32_t* tile);
 // compute units of the current device
 int current_cu_count();
 // ascending list of the set bits of bits[0..W) and their number

@@ -180,3 +180,36 @@ def test_sparse_union_costs_its_rows():
         time.append(best)
     say(f"full {time[0] * 1e3:.1f} us, none {time[1] * 1e3:.1f} us")
     assert time[1] <= time[0] / 3
+
+
+@pytest.mark.parametrize("B,L,d,n", [
+    # tokens, slots, columns, ids in all: none, one, around a GEMM1 tile, one less than the slots
+    (128, 5000, 72, 0), (130, 5000, 264, 1), (200, 30000, 520, 63), (300, 9000, 2056, 81),
+    (446, 28190, 2048, 1300), (700, 4000, 264, 3999), (600, 33000, 72, 500)])
+@pytest.mark.parametrize("dt,flags", [(BF16, 0), (F16, si.FLAG_EXACT_H)])
+def test_fewer_ids_than_slots(B, L, d, n, dt, flags):
+    """The slot-list path with its tiles chosen for the ids: each is some token's, spread over all
+    the slots and the first and last among them."""
+    say(f"few ids B={B} L={L} d={d} n={n} {dt} flags {flags}")
+    x, _, _, gu, dn, _ = problem(B, L, d, dt, pool=sparse_pool(L, "none"))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    slot = torch.randperm(L, device="cuda", generator=g)[:n]
+    if n > 1:
+        slot[:2] = torch.tensor([0, L - 1], device="cuda")
+    slot = slot.unique()
+    tok = torch.randint(0, B, slot.shape, device="cuda", generator=g).sort().values
+    idx = slot[torch.randperm(len(slot), device="cuda", generator=g)]
+    off = torch.zeros(B + 1, dtype=torch.int32, device="cuda")
+    off[1:] = torch.bincount(tok, minlength=B).cumsum(0)
+    assert idx.numel() < L
+    got = call(x, off, idx.to(torch.int32), gu, dn, flags=flags)
+    xx = x.double()[tok]                                  # a row an id
+    h = torch.nn.functional.silu((xx * gu[idx, 0].double()).sum(1)) * \
+        (xx * gu[idx, 1].double()).sum(1)
+    want = torch.zeros((B, d), dtype=torch.float64, device="cuda")
+    want.index_add_(0, tok, h[:, None] * dn[idx].double())
+    assert not got[torch.bincount(tok, minlength=B) == 0].any()
+    if n:
+        err = rel(got, want)
+        say(f"  {err:.2e}")
+        assert err <= (1e-4 if flags else ONE_H[dt])

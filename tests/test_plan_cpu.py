@@ -37,3 +37,24 @@ def test_noalloc_takes_what_64_token_tiles_fit(flags):
             assert need <= SCRATCH, (B, L, d)
             near += need > 0.8 * SCRATCH
     assert near > 100
+
+
+@pytest.mark.parametrize("flags", [0, si.FLAG_EXACT_H])
+def test_few_ids_take_the_tiles_of_their_number(flags):
+    """From 128 tokens, fewer ids than loaded slots: GEMM1's tile is that of a layer with as many
+    slots as there are ids; the K chunks and the workspace never exceed those of a full list."""
+    rng = random.Random(flags + 1)
+    fewer = 0
+    for _ in range(2000):
+        B, d, L = rng.randint(128, 3000), 8 * rng.randint(8, 700), rng.randint(1000, 40000)
+        nnz = rng.randint(0, L - 1)
+        few = si.selective_ffn_plan(B, nnz, L, d, flags=flags)
+        full = si.selective_ffn_plan(B, B * L, L, d, flags=flags)
+        if few[0] != 2:                                   # past the slot list's sizes
+            continue
+        assert few[1:3] == si.selective_ffn_plan(B, B * L, max(nnz, 1), d, flags=flags)[1:3]
+        assert few[5] <= full[5]
+        assert (si.selective_ffn_workspace(B, nnz, L, d, flags=flags) ==
+                si.selective_ffn_workspace(B, B * L, L, d, flags=flags))
+        fewer += few[1:5] != full[1:5]
+    assert fewer > 200
