@@ -37,7 +37,8 @@ namespace si {
 namespace {
 
 // Token tile by batch size: the smallest of 16, 32, 64 and 128 that holds the batch, since each
-// token tile streams the union's rows again (more than 128 tokens take tiles of 128).
+// token tile streams the union's rows again (more than 128 tokens take tiles of 128; few slots
+// two of 64, see make_plan).
 
 struct Plan {
     int64_t W;      // 32-bit words per token bitmap (slot s is bit s % 32 of word s / 32)
@@ -57,6 +58,13 @@ Plan make_plan(int64_t B, int64_t L, int64_t d, int num_cu) {
     p.W = (L + 31) / 32;
     p.Up = (L + kBK - 1) / kBK * kBK;
     p.bm = B > 64 ? 128 : (B > 32 ? 64 : (B > 16 ? 32 : 16));
+    // Where 32-slot work-groups of a 128-token tile would leave half the CUs idle, two tiles of 64
+    // tokens: twice the work-groups at half the work, and the second reading of a row is from L2
+    // (112 half tokens x 18 slots, d = 6224: 46 us with such tiles before the pipelined GEMMs, 57
+    // with 128; 127 tokens x 1250 slots, d = 5120 63.3 us with 128 and 48.1 with 64, x 4096 73.5
+    // and 58.9). Past 4096 slots it depends (65 and 127 tokens x 6000, d = 4096: 58.1 and 65.3 us
+    // with 128, 60.2 and 62.4 with 64).
+    if (p.bm == 128 && 2 * p.W <= num_cu) p.bm = 64;
     p.ntm = (int)((B + p.bm - 1) / p.bm);
     // GEMM1 slot tile: a work-group takes in (its tokens + its weight rows) x d, and a CU has
     // one at a time, so the least (rounds of work-groups) x (tokens + rows): with 303
@@ -206,7 +214,7 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
     if (e != hipSuccess) return e;
     const dim3 g2((unsigned)((int64_t)p.ntm * p.ntn * p.KS + 7) / 8 * 8);
     const dim3 g1((unsigned)(p.ntm * ((p.W * 32 + p.bn1 / 2 - 1) / (p.bn1 / 2)) + 7) / 8 * 8);
-    // (token tiles below 128 hold the whole batch)
+    // (token tiles below 64 hold the whole batch, and so do those of 64 with slot tiles over 32)
     const bool once = p.ntm == 1;
 #define SI_G1(BM, BN, WT, WW, NX, ONCE)                                                          \
     hipExtLaunchKernelGGL((gemm1_pipe<ET, kWord, BM, BN, WT, WW, NX, NX, ONCE>), g1,             \
@@ -236,7 +244,7 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
         case 32080: SI_G1(32, 80, 2, 1, 8, true); break;
         case 32096: SI_G1(32, 96, 2, 2, 8, true); break;
         case 32128: SI_G1(32, 128, 2, 2, 7, true); break;
-        case 64064: SI_G1(64, 64, 2, 2, 8, true); break;
+        case 64064: SI_G1_TILES(64, 64, 2, 2, 8); break;
         case 64080: SI_G1(64, 80, 4, 1, 8, true); break;
         case 64096: SI_G1(64, 96, 2, 2, 7, true); break;
         case 64128: SI_G1(64, 128, 2, 2, 6, true); break;
@@ -249,8 +257,8 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
         case 16128: SI_G2(16, 128, 1, 4, 8, 8, true); break;
         case 32128: SI_G2(32, 128, 1, 4, 6, 6, true); break;
         case 32256: SI_G2(32, 256, 1, 4, 4, 4, true); break;
-        case 64128: SI_G2(64, 128, 2, 2, 5, 5, true); break;
-        case 64256: SI_G2(64, 256, 2, 4, 3, 3, true); break;
+        case 64128: SI_G2_TILES(64, 128, 2, 2, 5, 5); break;
+        case 64256: SI_G2_TILES(64, 256, 2, 4, 3, 3); break;
         case 128128: SI_G2_TILES(128, 128, 4, 2, 3, 3); break;
         default: SI_G2_TILES(128, 256, 2, 4, 2, 3); break;
     }

@@ -94,7 +94,7 @@ def test_fast_h_is_one_value(B, d, dt):
 @pytest.mark.parametrize("B,L,d", [
     # the row-word GEMM2's token tiles of 16, 32, 64 and 128, with 128 and 256 columns
     (5, 3000, 520), (16, 900, 4104), (32, 3000, 520), (17, 3000, 2056), (64, 3000, 520),
-    (33, 3000, 2568), (127, 3000, 520), (65, 3000, 2312)])
+    (33, 3000, 2568), (127, 5000, 520), (65, 5000, 2312)])
 @pytest.mark.parametrize("dt", [BF16, F16])
 def test_fast_h_tiles(B, L, d, dt):
     say(f"FAST_H tiles B={B} L={L} d={d} {dt}")
@@ -105,6 +105,22 @@ def test_fast_h_tiles(B, L, d, dt):
     say(f"  {err:.2e}")
     assert err <= ONE_H[dt]
     assert torch.equal(got, call(*p[:5], flags=si.FLAG_FAST_H))
+
+
+@pytest.mark.parametrize("B,L,d", [
+    # up to 4096 slots, with 128 and 256 columns of GEMM2; the least, one word, an odd last tile
+    (65, 18, 4104), (100, 32, 520), (127, 1250, 2568), (66, 4096, 136), (127, 4095, 2312)])
+@pytest.mark.parametrize("dt", [BF16, F16])
+@pytest.mark.parametrize("flags", [0, si.FLAG_FAST_H])
+def test_two_tiles_of_64_tokens(B, L, d, dt, flags):
+    say(f"two 64-token tiles B={B} L={L} d={d} {dt} flags {flags}")
+    p = problem(B, L, d, dt)
+    got = call(*p[:5], flags=flags)
+    assert not got[3].any()
+    err = rel(got, p[5])
+    say(f"  {err:.2e}")
+    assert err <= (ONE_H[dt] if flags else 1e-4)
+    assert torch.equal(got, call(*p[:5], flags=flags))
 
 
 @pytest.mark.parametrize("B,L,d", [(128, 523800, 64), (130, 524288, 72), (260, 524000, 136)])

@@ -58,3 +58,13 @@ def test_few_ids_take_the_tiles_of_their_number(flags):
                 si.selective_ffn_workspace(B, B * L, L, d, flags=flags))
         fewer += few[1:5] != full[1:5]
     assert fewer > 200
+
+
+def test_few_slots_take_two_token_tiles():
+    """65 to 127 tokens: with few slots one token tile would leave half of 256 CUs without a
+    GEMM1 work-group."""
+    for L, tokens in ((1, 64), (18, 64), (4096, 64), (4097, 128), (9677, 128)):
+        for B in (65, 127):
+            plan = si.selective_ffn_plan(B, B * L, L, 5120)
+            assert (plan[0], plan[1], plan[3]) == (1, tokens, tokens), (B, L, plan)
+    assert si.selective_ffn_plan(64, 64 * 18, 18, 5120)[1] == 64
