@@ -13,7 +13,7 @@
 // Rows of up to 32768 keys (topk_rows_reg): thread t holds the C contiguous keys t*C .. in
 // registers, read once. The digits cover the range between the least and the largest candidate,
 // the search stops once the whole bin of T is taken (the lower bits cannot change the choice;
-// the selection then needs no scan of equal keys), and a bin of at most 64 candidates is ranked
+// the selection then needs no scan of equal keys), and a bin of at most 16 candidates is ranked
 // by one wave. The choice can also be written as a bitmap per row, or joined with a given set.
 // Longer rows (topk_rows) are read again in each of 4 passes of 8 bits.
 #include "common.h"
@@ -175,16 +175,18 @@ typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // NT threads a row, at least WPS waves a SIMD: two 1024-thread work-groups share a CU with 8
 // only, and the compiler must be told (left alone it takes 106 scalar registers for C = 8: 7
-// waves). digit: bits of a pass, at most kDigit.
-constexpr int kDigit = 11;
+// waves).
+constexpr int kDigit = 11, kBins = 1 << kDigit;  // bits and bins of a pass
+// Candidates that one wave ranks, a lane each: its loop over them is a chain that another pass
+// beats from about 20 on (128 rows of 2048 keys by value 7.3 / 6.0 / 5.8 us with 64 / 32 / 16)
+constexpr int kFew = 16;
 template <int C, int NT, int WPS>
 __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict__ scores,
                                                          int64_t L, int64_t ld, int64_t k,
-                                                         int mode, int digit, TopkOut o) {
+                                                         int mode, TopkOut o) {
     static_assert(32 % C == 0, "a thread's keys lie in one bitmap word");
     constexpr int NW = NT / kWave;
-    constexpr int kBins = 1 << kDigit;
-    constexpr int kOwn = kBins / NT;  // bins a thread adds up, at most
+    constexpr int kOwn = kBins / NT;  // bins a thread reads
     const int64_t b = blockIdx.x;
     const int t = threadIdx.x;
     const int lane = t & 63;
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict
     __shared__ uint32_t s_min[NW], s_max[NW];
     __shared__ int s_digit, s_take, s_n;
     __shared__ uint32_t s_key;
-    __shared__ uint32_t few[kWave];
+    __shared__ uint32_t few[kFew];
     __shared__ int n_few;
     __shared__ uint32_t jbits[kMaxRegKeys / 32];
     if (o.ulist) {  // the joined set as a bitmap
@@ -253,13 +255,12 @@ __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict
         kmin = s_min[q] < kmin ? s_min[q] : kmin;
         kmax = s_max[q] > kmax ? s_max[q] : kmax;
     }
-    // The k-th largest key T lies in [base, base + span]; a pass splits that into 2^digit
+    // The k-th largest key T lies in [base, base + span]; a pass splits that into 2^11
     // bins of 2^shift keys. (No candidates at all: nothing is counted, and the first pass ends it.)
     const uint32_t range = kmax - kmin;
     const int width = range ? 32 - __clz((int)range) : 0;
-    int shift = width > digit ? width - digit : 0;
+    int shift = width > kDigit ? width - kDigit : 0;
     uint32_t base = kmin, span = ~0u;
-    const int bins = 1 << digit, own = bins / NT;  // (NT <= 1024, digit >= 10)
     int take = (int)k;   // how many still to take among the candidates in the range
     bool done = k == 0;  // all of them are taken
     while (!done) {
@@ -280,17 +281,14 @@ __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict
         }
         if (cnt) atomicAdd(&hist[cur], cnt);
         __syncthreads();
-        // 2. the bins read (and cleared for the next pass): thread t owns `own` bins, the largest
+        // 2. the bins read (and cleared for the next pass): thread t owns kOwn bins, the largest
         //    digits in the lowest threads, and a block-wide scan counts the keys above
         int c[kOwn], sum = 0;
 #pragma unroll
         for (int e = 0; e < kOwn; ++e) {
-            c[e] = 0;
-            if (e < own) {
-                const int bin = bins - 1 - own * t - e;
-                c[e] = hist[bin];
-                hist[bin] = 0;
-            }
+            const int bin = kBins - 1 - kOwn * t - e;
+            c[e] = hist[bin];
+            hist[bin] = 0;
             sum += c[e];
         }
         int all;
@@ -304,7 +302,7 @@ __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict
 #pragma unroll
         for (int e = 0; e < kOwn; ++e) {
             if (above < take && above + c[e] >= take) {
-                s_digit = bins - 1 - own * t - e;
+                s_digit = kBins - 1 - kOwn * t - e;
                 s_take = take - above;
                 s_n = c[e];
             }
@@ -317,10 +315,10 @@ __global__ __launch_bounds__(NT, WPS) void topk_rows_reg(const float* __restrict
         const int n = s_n;  // candidates in the bin
         done = take == n;
         if (done || shift == 0) break;
-        shift = shift > digit ? shift - digit : 0;
-        if (n > kWave) continue;
-        // 4. no more candidates than lanes: they are gathered, one a lane, and one wave ranks
-        //    them by comparing each with all (all waves at it take 1 us longer)
+        shift = shift > kDigit ? shift - kDigit : 0;
+        if (n > kFew) continue;
+        // 4. few candidates: they are gathered, one a lane, and one wave ranks them by comparing
+        //    each with all (all waves at it take 1 us longer)
 #pragma unroll
         for (int j = 0; j < C; ++j)
             if (((cand >> j) & 1u) && key[j] - base <= span) few[atomicAdd(&n_few, 1)] = key[j];
@@ -402,19 +400,16 @@ namespace {
 // keys. What a row costs beside its keys goes by the work-group's threads (scans over the waves,
 // barriers, bins), so rows of few keys take 512 of them, and so do rows of up to 4096 keys where a
 // CU has more than one; with fewer rows than CUs a row of more than 2048 is quicker with 1024 (256
-// rows of 3000 keys by |value| 7.2 / 6.3 us with 512 / 1024 threads, of 2047 5.8 / 5.7; 300 rows
-// of 3000 8.0 / 10.5, of 64 3.9 / 5.3). Rows of 4097 to 8192 keys on shared CUs need 8 waves a
+// rows of 3000 keys by |value| 6.9 / 6.3 us with 512 / 1024 threads, of 2047 5.6 / 5.7; 300 rows
+// of 3000 7.8 / 10.5, of 64 4.0 / 5.3). Rows of 4097 to 8192 keys on shared CUs need 8 waves a
 // SIMD (300 rows of 4500 keys 14.8 / 12.6 us, of 7706 17.0 / 14.8), which costs 0.7 us where a CU
 // has one.
-// Passes of 11 bits by |value| and for counts; 10 by value, whose keys span both signs (256 rows
-// of 3000 keys by value 6.5 / 8.3 us with 10 / 11 bits, of 7706 by |value| 10.8 / 9.7).
 bool launch_reg(const float* scores, int64_t B, int64_t L, int64_t ld, int64_t k, int mode,
                 const TopkOut& o, hipStream_t s) {
-    const int digit = mode == 1 ? 10 : kDigit;
     const bool shared_cu = B > current_cu_count();
 #define SI_TOPK(C, NT, WPS)                                                                      \
     hipLaunchKernelGGL((topk_rows_reg<C, NT, WPS>), dim3((unsigned)B), dim3(NT), 0, s, scores, L, \
-                       ld, k, mode, digit, o)
+                       ld, k, mode, o)
     if (L <= 512)
         SI_TOPK(1, 512, 1);
     else if (L <= 1024)

@@ -202,9 +202,9 @@ def test_residual_rmsnorm(xdt, d):
 @pytest.mark.parametrize("L", [70, 1023, 4097, 20000, 32768])
 def test_topk_bins(L):
     """The search by 11-bit bins of the candidates' range at its edges: ranges of one key, below,
-    at and above 2^11 and 2^22 keys and the whole line (NaN, both infinities, both signs); 64 and
-    65 candidates in the bin of the k-th key (ranked in a wave, or split again); runs of equal
-    keys across it; k around every such place."""
+    at and above 2^11 and 2^22 keys and the whole line (NaN, both infinities, both signs); 16,
+    17, 64 and 65 candidates in the bin of the k-th key (up to 16 are ranked in a wave, more split
+    again); runs of equal keys across it; k around every such place."""
     rng = np.random.default_rng(L)
     rows = []
     for span in (1, 2, 2**11 - 1, 2**11, 2**11 + 1, 2**22, 2**22 + 1, 2**30):
@@ -213,7 +213,7 @@ def test_topk_bins(L):
     whole = rng.integers(0, 2**32, L, dtype=np.uint64).astype(np.uint32).view(np.float32)
     whole[:6] = [np.nan, np.inf, -np.inf, 0.0, -0.0, np.float32(1e-45)]
     rows.append(whole)
-    for m in (64, 65):  # m neighbours in one bin of a range that a far key opens
+    for m in (16, 17, 64, 65):  # m neighbours in one bin of a range that a far key opens
         few = np.full(L, 1.0, np.float32)
         few[: m] = np.nextafter(np.float32(2.0), np.float32(3.0))
         few[: m // 2] = np.nextafter(few[0], np.float32(3.0))
@@ -221,7 +221,7 @@ def test_topk_bins(L):
         rows.append(rng.permutation(few))
     x = np.stack(rows)
     dx = dev_tensor(x)
-    for k in sorted({1, 2, 31, 33, 63, 64, 65, 66, 67, L // 3, L - 1, L}):
+    for k in sorted({1, 2, 15, 16, 17, 18, 31, 33, 63, 64, 65, 66, 67, L // 3, L - 1, L}):
         for mode in ("raw", "abs"):
             say(f"topk bins L={L} k={k} {mode}")
             got = host_array(si.select_topk(dx, k, mode))
