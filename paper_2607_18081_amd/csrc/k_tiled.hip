@@ -249,12 +249,15 @@ TPlan make_tplan(int64_t B, int64_t L, int64_t d, int num_cu, bool exact) {
     return p;
 }
 
-// The plan a call takes. Its nnz ids are at most nnz slots of the union: with fewer ids than slots
-// the tiles are chosen for those, in the workspace of all (446 half tokens with 3 ids each of 28190
-// slots, d = 2048: 82.3 us with the tiles for all, 51.8 so; 622 x 3 of 26818, d = 512 57.7 / 43.2).
+// The plan a call takes. Its nnz ids are at most nnz slots of the union: with fewer than a third
+// as many ids as slots the tiles are chosen for those, in the workspace of all (446 half tokens
+// with 3 ids each of 28190 slots, d = 2048: 82.3 us with the tiles for all, 51.8 so; 622 x 3 of
+// 26818, d = 512 57.7 / 43.2). Of random sets with fewer, a half is over 4% faster and 1 in 500
+// slower; from 0.4 on the ids say less of the union (often half of them), and 1 in 25 is slower, by
+// up to a quarter, where the rounds of work-groups for it fall badly.
 TPlan launch_tplan(int64_t B, int64_t nnz, int64_t L, int64_t d, int num_cu, bool exact) {
     TPlan p = make_tplan(B, L, d, num_cu, exact);
-    if (nnz < L) pick_tiles(p, B, nnz > 0 ? nnz : 1, d, num_cu, exact, p.KS);
+    if (3 * nnz < L) pick_tiles(p, B, nnz > 0 ? nnz : 1, d, num_cu, exact, p.KS);
     return p;
 }
 

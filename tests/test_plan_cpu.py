@@ -41,13 +41,14 @@ def test_noalloc_takes_what_64_token_tiles_fit(flags):
 
 @pytest.mark.parametrize("flags", [0, si.FLAG_EXACT_H])
 def test_few_ids_take_the_tiles_of_their_number(flags):
-    """From 128 tokens, fewer ids than loaded slots: GEMM1's tile is that of a layer with as many
-    slots as there are ids; the K chunks and the workspace never exceed those of a full list."""
+    """From 128 tokens, ids for less than a third of the loaded slots: GEMM1's tile is that of a
+    layer with as many slots as there are ids; the K chunks and the workspace never exceed those of
+    a full list."""
     rng = random.Random(flags + 1)
     fewer = 0
     for _ in range(2000):
         B, d, L = rng.randint(128, 3000), 8 * rng.randint(8, 700), rng.randint(1000, 40000)
-        nnz = rng.randint(0, L - 1)
+        nnz = rng.randint(0, (L - 1) // 3)
         few = si.selective_ffn_plan(B, nnz, L, d, flags=flags)
         full = si.selective_ffn_plan(B, B * L, L, d, flags=flags)
         if few[0] != 2:                                   # past the slot list's sizes
@@ -57,6 +58,7 @@ def test_few_ids_take_the_tiles_of_their_number(flags):
         assert (si.selective_ffn_workspace(B, nnz, L, d, flags=flags) ==
                 si.selective_ffn_workspace(B, B * L, L, d, flags=flags))
         fewer += few[1:5] != full[1:5]
+        assert si.selective_ffn_plan(B, L // 3 + 1, L, d, flags=flags) == full
     assert fewer > 200
 
 
