@@ -146,9 +146,9 @@ def test_per_token_ragged_shapes(d, wdtype):
                                    (32, 264, 613), (33, 512, 613), (64, 264, 613),
                                    (70, 1000, 613), (3, 72, 16500)])
 def test_union_path_ragged(B, d, L):
-    """Row-word GEMM path (SI_FLAG_UNION below 5 tokens); L = 16500 gives over 512 bitmap
-    words, where a work-group takes both 16-row tiles of a word, and the smaller ones one tile
-    each. Without the flag, 2 and 3 tokens take the per-token path, to the same result."""
+    """Row-word GEMM path (SI_FLAG_UNION below 5 tokens) at every token tile; L = 16500 gives slot
+    tiles of 64, the smaller ones of 32. Without the flag, 2 and 3 tokens take the per-token path,
+    to the same result."""
     N = L + 287
     say(f"union ragged B={B} d={d} L={L}")
     rng, draw, ref, gpu = _rand_problem(B * 1000 + d, N, d, L, "bf16")
@@ -175,9 +175,9 @@ def test_union_path_ragged(B, d, L):
                                            (160, 2048, 2100, False), (130, 6144, 700, False)])
 def test_union_tiled_ragged(B, d, L, sparse):
     """Batches of 128 tokens and more take the LDS-tiled GEMMs: ragged token, slot and K tiles,
-    a union much smaller than L (sparse), split-K tails, empty sets. The last four shapes run
-    GEMM2 on its XCD grid (combo counts 8, 8, 16, 8) with 128-, 160-, 128- and 192-column
-    tiles, the first two with a ragged last column tile."""
+    a union much smaller than L (sparse), split-K tails, empty sets. The first three shapes have
+    a ragged last column tile and the last four many column tiles, of which d = 4088 and 5112 end in
+    a ragged one."""
     N = L + 97
     say(f"union tiled B={B} d={d} L={L} sparse={sparse}")
     rng, draw, ref, gpu = _rand_problem(B * 7 + d + L, N, d, L, "bf16")
@@ -215,10 +215,10 @@ def test_union_tiled_ragged(B, d, L, sparse):
 
 @pytest.mark.parametrize("d", [64, 128, 192, 256, 320, 384, 448])
 def test_union_tiled_k_step_counts(d):
-    """The 256-token GEMM1 keeps three K tiles in flight in rotating register sets and runs the
-    one or two steps left over after its loop; GEMM2 keeps two or three. d = 64 .. 448 gives 1
-    to 7 K steps in GEMM1, and union sizes around multiples of 64 give GEMM2 chunks of every
-    remainder; each against the oracle and against the pair form of h."""
+    """The GEMMs keep two to four K steps in flight in rotating LDS stages and run what is left of
+    a turn of the stages after their loops. d = 64 .. 448 gives 1 to 7 K steps in GEMM1, and union
+    sizes around multiples of 64 give GEMM2 chunks of every remainder; each against the oracle and
+    against the pair form of h."""
     B, L = 200, 700
     N = L + 50
     say(f"tiled K steps d={d}")
@@ -237,7 +237,8 @@ def test_union_tiled_k_step_counts(d):
         assert max_rel_l2(exact, want) <= ALARM_PER_TOKEN, nU
 
 
-@pytest.mark.parametrize("B,L,d,step", [
+# tokens, slots, d, and every how many slots one is used
+TILED_SHAPES = [
     # GEMM1 tiles (tokens x weight rows) by what fills the CUs: 128 x 160, 128 x 256, 256 x 160,
     # 256 x 192, 256 x 256
     (130, 1290, 8, 1), (512, 5300, 72, 1), (500, 9001, 72, 1), (600, 7300, 200, 1),
@@ -247,10 +248,14 @@ def test_union_tiled_k_step_counts(d):
     (1100, 5300, 832, 1), (200, 1290, 320, 1), (200, 1290, 520, 1),
     # slots so far apart that a tile's mask words do not fit its LDS window
     (1100, 5300, 136, 7), (512, 5300, 72, 9), (130, 9000, 136, 40),
-    # GEMM2's 256 x 256 tile and split K, a ragged last column tile
-    (2048, 5500, 4088, 1),
+    # GEMM2's 256 x 128 tile (128 x 256 with the pair) in one chunk and its 256 x 256 tile, a ragged
+    # last column tile
+    (2048, 5500, 4088, 1), (2500, 1000, 5112, 1),
     # the union list from its own kernel (many tokens, many slots), and the largest GEMM1 scans
-    (2060, 700, 72, 1), (128, 33000, 64, 1), (131, 32768, 64, 3)])
+    (2060, 700, 72, 1), (128, 33000, 64, 1), (131, 32768, 64, 3)]
+
+
+@pytest.mark.parametrize("B,L,d,step", TILED_SHAPES)
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
 def test_union_tiled_tiles(B, L, d, step, dt):
     """Every tile of the tiled GEMMs at ragged token, slot, column and K edges, against the
@@ -287,12 +292,17 @@ def test_union_tiled_tiles(B, L, d, step, dt):
         assert torch.equal(got, si.selective_ffn(x, off, idx, gu, dn, flags=flags, workspace=ws))
 
 
-@pytest.mark.parametrize("B,L,d", [
+WORD_SHAPES = [
     # token tiles of 16, 32, 64 and 128 at their edges; slot tiles of 32, 40, 48 and 64 by the
     # number of loaded slots; GEMM2 column tiles of 128 (d <= 2048 or 16 tokens) and 256
     (5, 600, 520), (16, 9000, 136), (16, 11000, 72), (16, 16000, 264), (17, 8200, 2056),
     (32, 11000, 200), (32, 13001, 64), (33, 8190, 2568), (64, 9677, 328), (64, 12280, 72),
-    (64, 15999, 136), (65, 8192, 448), (127, 10000, 2312), (127, 12000, 104), (127, 16383, 8)])
+    (64, 15999, 136), (65, 8192, 448), (127, 10000, 2312), (127, 12000, 104), (127, 16383, 8),
+    # 32 tokens x 32 slots; two tiles of 64 tokens
+    (32, 8000, 72), (100, 4000, 264)]
+
+
+@pytest.mark.parametrize("B,L,d", WORD_SHAPES)
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
 def test_union_word_tiles(B, L, d, dt):
     """Every tile of the row-word GEMMs at ragged token, slot, column and K edges, against the

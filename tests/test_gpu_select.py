@@ -311,3 +311,41 @@ def test_select_errors():
         si.merge_scores(torch.zeros((2, 5), dtype=torch.float64, device="cuda"), [1, 0])
     with pytest.raises(ValueError):
         si.merge_scores(torch.zeros((2, 5), dtype=torch.float32, device="cuda"), [1, 1])
+
+
+# tokens, slots, d: each tile of the MFMA kernel (128 x 160, 128 x 256, 256 x 160, 256 x 192 and
+# 256 x 256 tokens x weight rows) at ragged tokens, slots and K
+ACT_SHAPES = [(130, 701, 520), (257, 7301, 136), (300, 9001, 72), (500, 9001, 136),
+              (1100, 4001, 72), (513, 7301, 264), (257, 11003, 72), (1100, 5303, 136),
+              (257, 14335, 72)]
+
+
+@pytest.mark.parametrize("T,L,d", ACT_SHAPES)
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_activation_tiles(T, L, d, dt):
+    """Eq. 1 scores and the per-token counts of the dynamic set from every tile of the MFMA
+    kernel, against the definition in float64 on the GPU: scores to 1e-5 each slot (a few hundred
+    float32 |a|, each within a few parts in 10^6 of the largest), every slot's count between its
+    sure picks and those plus the keys within 1e-4 of a token's boundary, as above."""
+    say(f"activation tiles T={T} L={L} d={d} {dt}")
+    g = torch.Generator(device="cuda").manual_seed(T + L + d)
+    gu = torch.empty((L, 2, d), device="cuda").normal_(0, d ** -0.5, generator=g).to(dt)
+    x = torch.empty((T, d), device="cuda").normal_(0, 1.0, generator=g).to(dt)
+    xx = x.double()
+    a = (torch.nn.functional.silu(xx @ gu[:, 0].double().t()) * (xx @ gu[:, 1].double().t())).abs()
+    want = a.sum(0)
+    got = si.profile_scores(x, gu)
+    err = ((got - want).abs() / want).max().item()
+    say(f"  scores {err:.2e}")
+    assert err <= 1e-5
+    assert torch.equal(got, si.profile_scores(x, gu))
+    static = torch.randperm(L, device="cuda", generator=g)[:L // 3].to(torch.int32)
+    alpha = L // 4
+    _, counts = si.dynamic_set(x, gu, static, alpha, L // 2)
+    edge = a.topk(alpha, dim=1).values[:, -1:]
+    sure = (a > edge * (1 + 1e-4)).sum(0)
+    maybe = (a >= edge * (1 - 1e-4)).sum(0)
+    counts = counts.to(sure)
+    say(f"  counts with an allowance: {int((sure != maybe).sum())} of {L}")
+    assert bool(((sure <= counts) & (counts <= maybe)).all())
+    assert int(counts.sum()) == T * alpha

@@ -70,3 +70,28 @@ def test_few_slots_take_two_token_tiles():
             plan = si.selective_ffn_plan(B, B * L, L, 5120)
             assert (plan[0], plan[1], plan[3]) == (1, tokens, tokens), (B, L, plan)
     assert si.selective_ffn_plan(64, 64 * 18, 18, 5120)[1] == 64
+
+
+GEMM1_TILES = {(256, 256), (256, 192), (256, 160), (128, 256), (128, 160)}
+
+
+def test_value_checks_reach_every_tile():
+    """The shapes whose values the GPU tests check take every tile of the pipelined GEMMs on 256
+    CUs, so that a changed tile choice cannot leave one unchecked."""
+    from tests.test_gpu_ffn import TILED_SHAPES, WORD_SHAPES
+    from tests.test_gpu_select import ACT_SHAPES
+    plan = lambda B, L, d, flags=0: si.selective_ffn_plan(B, B * L, L, d, flags=flags)
+    one = [plan(B, L, d) for B, L, d, step in TILED_SHAPES]
+    pair = [plan(B, L, d, si.FLAG_EXACT_H) for B, L, d, step in TILED_SHAPES]
+    assert {p[0] for p in one + pair} == {2}
+    assert {p[1:3] for p in one} == {p[1:3] for p in pair} == GEMM1_TILES
+    assert {p[3:5] for p in one} == {(256, 256), (256, 128), (128, 128)}
+    assert {p[3:5] for p in pair} == {(128, 256), (128, 128)}
+    word = [plan(B, L, d) for B, L, d in WORD_SHAPES]
+    assert {p[0] for p in word} == {1}
+    assert {p[1:3] for p in word} == {(t, r) for t in (16, 32, 64, 128) for r in (64, 80, 96, 128)}
+    assert {p[3:5] for p in word} == {(16, 128)} | {(t, c) for t in (32, 64, 128)
+                                                    for c in (128, 256)}
+    # (a batch in one token tile, and in two)
+    assert {(p[1], -(-B // p[1])) for p, (B, _, _) in zip(word, WORD_SHAPES)} >= {(64, 1), (64, 2)}
+    assert {si.activations_plan(T, L) for T, L, _ in ACT_SHAPES} == GEMM1_TILES
