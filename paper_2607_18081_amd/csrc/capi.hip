@@ -104,10 +104,11 @@ int topk_key(int mode) {
 }
 
 // Smallest batch that takes the union path by default. Reading the union once costs |U| rows
-// instead of nnz >= |U|, but the union path runs four kernels with a fixed cost of about
-// 11 000 row reads (measured on the 7B shape: a step is about 28.5 us + 3.6 ns per union row,
-// against 8 us + 2.5 ns per active row on the per-token path). With the workloads' overlap
-// the two meet between B = 4 (36.5 us per-token, 43.0 us union) and B = 6 (55.0 / 45.8 us).
+// instead of nnz >= |U|, but the union path has four kernels instead of two and carries h as a hi +
+// lo pair instead of float32. Four tokens (a work-group per CU, 64 a token) are the per-token path's
+// last good size: 7706 slots with 30% active, d = 4096 33.9 us per token and 38.2 by the union with
+// 4 tokens, 51.4 and 38.9 with 5; 14336 slots 60.1 and 60.0, 88.8 and 61.9; 9677, d = 5120 52.9 and
+// 53.8, 78.7 and 55.6. (2000 slots, d = 4096: per token up to 8, 19.9 and 27.1 us.)
 constexpr int64_t kUnionMinB = 5;
 
 bool use_union(int64_t B, int64_t L, int64_t d, si_dtype xdt, si_dtype wdt, int flags) {

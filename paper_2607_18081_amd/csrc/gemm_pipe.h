@@ -771,8 +771,8 @@ __global__ __launch_bounds__(64 * WT * WW) void gemm2_pipe(
     for (int i = 0; i < FW; ++i)
 #pragma unroll
         for (int j = 0; j < FT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // hi + lo: K in runs, as in GEMM1's kWord (the 128 x 256 tile has no registers for it; its
-    // chunks are short)
+    // hi + lo: K in runs, as in GEMM1's kWord (the 128 x 256 tile has no registers for it and sums
+    // its chunk, the shortest that the workspace allows, in one)
     constexpr bool kRuns = PL == 2 && FT * FW < 16;
     const int run = kRuns ? run_steps(2 * ((ke - kb + kBK - 1) / kBK)) / 2 + 1 : 0;
     int left = run;

@@ -205,8 +205,11 @@ void pick_tiles(TPlan& p, int64_t B, int64_t U, int64_t d, int num_cu, bool exac
         const G2Tile& tl = exact ? kG2Exact[c] : kG2Tiles[c];
         const int64_t tiles = cdiv(B, tl.bm) * cdiv(d, tl.bn);
         // (the pair's 256-column tile sums a chunk in one run, for want of registers: it is taken
-        // with short chunks only. 512 half tokens, d = 5120: 8.6e-7 from the 64-bit result in
-        // 3 such chunks, 7.1e-7 with 128 columns and runs)
+        // with the most chunks only, so that no run is longer than it has to be. Distance from the
+        // 64-bit result in such runs and with 128 columns in runs of about the square root: 512
+        // half tokens x 9677 slots, d = 5120, 3 chunks 8.6e-7 and 7.1e-7; 2048 x 7706, d = 4096,
+        // where one chunk is all there is, 9.9e-7 and 6.5e-7 in half, 2.62e-6 and 2.53e-6 in bf16,
+        // 417 and 445 us, 393 and 433 us)
         for (int64_t ks = exact && c == 0 ? rows : 1; ks <= rows && ks <= steps; ++ks) {
             const double cost = (double)(cdiv(tiles * ks, num_cu) * cdiv(steps, ks) * tl.cost) +
                                 2e-4 * (double)(B * d) * (double)(ks - 1) + (ks > 1 ? 300. : 0.);

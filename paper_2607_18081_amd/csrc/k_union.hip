@@ -14,12 +14,13 @@
 //
 // Kernels (the GEMMs are gemm_pipe.h's, without a union list):
 //  - token bitmaps: one work-group per token marks its active slots in an L-bit bitmap;
-//  - gemm1_pipe in its kWord mode: one work-group per 32-slot bitmap word and tile of tokens. It
-//    ORs the word over its tokens; rows of slots that none of them has load nothing (their
-//    loads are out of range). H is written by slot, zero outside the tokens' sets;
-//  - gemm2_pipe over K = slot: a tile of tokens x 256 columns, one of KS chunks of slots, down
-//    rows outside the union again without memory traffic. The KS sums are added in a fixed
-//    order (chunk 0 goes to y itself).
+//  - gemm1_pipe in its kWord mode: one work-group per tile of 32, 40, 48 or 64 slots and tile of
+//    tokens. It ORs the slots' bitmap words over its tokens; rows of slots that none of them has
+//    load nothing (their loads are out of range), and a tile without any writes zeros and ends. H
+//    is written by slot, zero outside the tokens' sets;
+//  - gemm2_pipe over K = slot: a tile of tokens x 128 or 256 columns, one of KS chunks of slots,
+//    down rows outside the union again without memory traffic, steps of 64 slots without any
+//    passed over. The KS sums are added in a fixed order (chunk 0 goes to y itself).
 // For so few tokens both GEMMs stream the union's rows: they are bound by how much of HBM's
 // latency the loads in flight cover, so the tiles are small and the stages many (70 to 160 KB
 // of LDS a CU), and the row loads carry the non-temporal policy while one token tile reads each
@@ -163,9 +164,12 @@ hipError_t launch_token_bitmaps(const int32_t* offsets, const int32_t* idx, int6
     return hipGetLastError();
 }
 
-// batches from which the LDS-tiled GEMMs (k_tiled.hip) take over: below, the weights are
-// streamed once and the row-word kernels here are bandwidth bound; above, reuse across the
-// batch makes the products compute bound
+// Batches from which the LDS-tiled GEMMs (k_tiled.hip) take over, and with them h as one 16-bit
+// value, half of H's workspace. Past 128 tokens the row-word kernels read every row once per token
+// tile: 129 tokens x 7706 slots, d = 4096 78 us tiled and 86 by words, x 9677, d = 5120 101 and 147.
+// 128 tokens fit one token tile and would be faster by words (88 and 71 us, 110 and 95, with the
+// hi + lo pair), as would up to 256 tokens over 2000 slots (d = 4096: 71 and 46 us), but the form of
+// h from 128 tokens on, and what fits a given scratch there, are part of the interface.
 constexpr int64_t kTiledMinB = 128;
 
 static bool use_tiled(int64_t B, int64_t L, int64_t d) {
