@@ -22,7 +22,7 @@
 //    down rows outside the union again without memory traffic, steps of 64 slots without any
 //    passed over. The KS sums are added in a fixed order (chunk 0 goes to y itself).
 // For so few tokens both GEMMs stream the union's rows: they are bound by how much of HBM's
-// latency the loads in flight cover, so the tiles are small and the stages many (70 to 160 KB
+// latency the loads in flight cover, so the tiles are small and the stages many (60 to 160 KB
 // of LDS a CU), and the row loads carry the non-temporal policy while one token tile reads each
 // row (128 tokens x 524288 slots, d = 512 556 us, default policy 575; with several tiles the
 // others then find fewer rows in L2: 300 tokens x 523900, d = 680 2267 / 2156 us).
@@ -258,7 +258,10 @@ hipError_t launch_union_t(const void* x, int64_t B, int64_t d, const int32_t* of
         default: SI_G1_TILES(128, 128, 2, 2, 4); break;
     }
     switch (p.bm * 1000 + p.bn2) {
-        case 16128: SI_G2(16, 128, 1, 4, 8, 8, true); break;
+        // (three stages: eight, and no wait for the union words to hold them back, read HBM more
+        // slowly. 16 tokens x 7706 slots, d = 4096 45.3 / 44.6 / 44.4 / 43.7 / 48.4 us with 8, 6, 4,
+        // 3 and 2 stages, x 28672, d = 5120 172.2 / 171.2 / 170.2 / 169.0 with 8, 6, 4 and 3)
+        case 16128: SI_G2(16, 128, 1, 4, 3, 3, true); break;
         case 32128: SI_G2(32, 128, 1, 4, 6, 6, true); break;
         case 32256: SI_G2(32, 256, 1, 4, 4, 4, true); break;
         case 64128: SI_G2_TILES(64, 128, 2, 2, 5, 5); break;
